@@ -111,6 +111,15 @@ hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t
                           hipStream_t stream);
 hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t *info, double tol,
                               int32_t max_iter, hipStream_t stream);
+// Systems at the front of the order, a workgroup of `waves` (4 or 8)
+// wavefronts each (lu_block.hip).
+hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_t mixed, int32_t *info,
+                           hipStream_t stream);
+hipError_t launch_refine_block(const WsView &v, int32_t count, int32_t waves, int32_t *info, double tol,
+                               int32_t max_iter, hipStream_t stream);
+// A whole batch in one persistent launch (lu_batch.hip).
+hipError_t launch_lu_batch(const WsView &v, int32_t grid, int32_t B, int32_t n_block, int32_t mixed, double tol,
+                           int32_t max_iter, int32_t *info, hipStream_t stream);
 hipError_t launch_forces(const WsView &v, int32_t B, int32_t max_k, double *gamma, double *cp,
                          double *cl, double *cl_p, hipStream_t stream);
 // Viscous correction (viscous.hip): one wavefront per (airfoil, angle).
