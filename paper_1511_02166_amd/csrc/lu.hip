@@ -44,7 +44,7 @@ bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
 }  // namespace
 
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
-                               int32_t mixed, double tol, int32_t max_iter, int32_t *info,
+                               int32_t max_k, int32_t mixed, double tol, int32_t max_iter, int32_t *info,
                                int32_t persistent, int32_t wg_waves, hipStream_t stream) {
     hipError_t e = hipSuccess;
     if (persistent && (n_block == 0 || !eight_waves(n_block, max_n1_block, wg_waves == 0 ? 4 : wg_waves))) {
@@ -60,11 +60,22 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
     e = launch_lu_wave(v, n_block, B - n_block, mixed, info, stream);
     if (e != hipSuccess) return e;
     if (mixed) {
-        if (n_block > 0) {
-            e = launch_refine_block(v, n_block, waves, info, tol, max_iter, stream);
+        e = launch_refine_block(v, 0, n_block, 1, max_n1_block, max_k, waves, info, tol, max_iter, stream);
+        if (e != hipSuccess) return e;
+        // Small systems: a workgroup each where it reads the matrix for
+        // several right-hand sides (2048 systems of order 201, four angles:
+        // 1.96 -> 0.99 ms) or where the batch leaves most SIMDs idle (256 of
+        // order 129: 84 -> 60 us, 512: 46 -> 41, but 1024: 106 -> 170); a
+        // wavefront each otherwise, and where the tiling fixes the
+        // workgroups.
+        const int32_t n_small = B - n_block;
+        const int32_t kw = wg_waves != 0 ? PANEL_KMAX : n_small <= 2 * device_cus() ? 0 : 1;
+        if (max_k > kw) {
+            e = launch_refine_block(v, n_block, n_small, kw + 1, PANEL_WAVE_MAX_N1, max_k, 4, info, tol,
+                                    max_iter, stream);
             if (e != hipSuccess) return e;
         }
-        e = launch_refine_wave(v, n_block, B - n_block, info, tol, max_iter, stream);
+        if (kw > 0) e = launch_refine_wave(v, n_block, n_small, kw, info, tol, max_iter, stream);
     }
     return e;
 }

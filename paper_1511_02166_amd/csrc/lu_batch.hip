@@ -24,7 +24,7 @@ template <typename T> struct BatchWaveLds {
 };
 template <typename T> union BatchLds {
     blk::BlkLds<T, TPB> lu;
-    WgRefLds<TPB> ref;
+    rfb::WgRefLds<TPB, 4, 768> ref;
     BatchWaveLds<T> wave[TPB / 64];
 };
 
@@ -37,7 +37,7 @@ __device__ __forceinline__ void batch_wg_item(const WsView &v, int b, int32_t *i
     blk::blk_lu<T, TPB, 3>(v, b, info, S.lu);
     __syncthreads();
     if (mixed) {
-        wg_refine<TPB>(v, b, info, tol, max_iter, S.ref);
+        rfb::wg_refine<TPB, 4, 768>(v, b, info, tol, max_iter, S.ref);
         __syncthreads();
     }
 }

@@ -1,8 +1,6 @@
 // lu_block.hip -- kernels that run one workgroup per airfoil over the first
-// entries of the plan's order: the factorisation + solve (lu_block_impl.hpp)
-// and the refinement of FP32 factors (refine_block_impl.hpp).
+// entries of the plan's order: the factorisation + solve (lu_block_impl.hpp).
 #include "lu_block_impl.hpp"
-#include "refine_block_impl.hpp"
 
 namespace panel {
 namespace {
@@ -13,13 +11,6 @@ template <typename T, int RMAX, int TB>
 __global__ __launch_bounds__(TB, 2) void lu_kernel(WsView v, int32_t *__restrict__ info_out) {
     __shared__ blk::BlkLds<T, TB> S;
     blk::blk_lu<T, TB, RMAX>(v, v.order[blockIdx.x], info_out, S);
-}
-
-template <int TB>
-__global__ __launch_bounds__(TB) void refine_kernel(WsView v, int32_t *__restrict__ info, double tol,
-                                                     int max_iter) {
-    __shared__ WgRefLds<TB> S;
-    wg_refine<TB>(v, v.order[blockIdx.x], info, tol, max_iter, S);
 }
 
 template <typename T>
@@ -39,16 +30,6 @@ hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_
         launch_lu<float>(v, count, waves, info, stream);
     else
         launch_lu<double>(v, count, waves, info, stream);
-    return hipGetLastError();
-}
-
-hipError_t launch_refine_block(const WsView &v, int32_t count, int32_t waves, int32_t *info, double tol,
-                               int32_t max_iter, hipStream_t stream) {
-    if (count <= 0) return hipSuccess;
-    if (waves == 8)
-        refine_kernel<512><<<count, 512, 0, stream>>>(v, info, tol, max_iter);
-    else
-        refine_kernel<256><<<count, 256, 0, stream>>>(v, info, tol, max_iter);
     return hipGetLastError();
 }
 

@@ -14,10 +14,12 @@ __global__ __launch_bounds__(WL, 2) void lu_wave_kernel(WsView v, int32_t first,
     wave_lu<T>(v, v.order[first + blockIdx.x], info_out, W);
 }
 
-__global__ __launch_bounds__(WL, 2) void refine_wave_kernel(WsView v, int32_t first, int32_t *__restrict__ info,
-                                                         double tol, int max_iter) {
+__global__ __launch_bounds__(WL, 2) void refine_wave_kernel(WsView v, int32_t first, int32_t kmax,
+                                                         int32_t *__restrict__ info, double tol, int max_iter) {
     __shared__ WaveRefLds W;
-    wave_refine(v, v.order[first + blockIdx.x], info, tol, max_iter, W);
+    const int b = v.order[first + blockIdx.x];
+    if (v.meta[b].K > kmax) return;
+    wave_refine(v, b, info, tol, max_iter, W);
 }
 
 }  // namespace
@@ -32,10 +34,10 @@ hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t *info, double tol,
+hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t kmax, int32_t *info, double tol,
                               int32_t max_iter, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    refine_wave_kernel<<<count, WL, 0, stream>>>(v, first, info, tol, max_iter);
+    refine_wave_kernel<<<count, WL, 0, stream>>>(v, first, kmax, info, tol, max_iter);
     return hipGetLastError();
 }
 

@@ -371,7 +371,7 @@ panel_status panel_factor_solve(const panel_plan *plan, void *ws, double refine_
     if (plan->order_stale)
         return fail(PANEL_EINVAL, "wave limit changed: call panel_workspace_init before factoring");
     WsView v = ws_view(ws, plan->layout);
-    hipError_t e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, mixed, refine_tol,
+    hipError_t e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, plan->max_k, mixed, refine_tol,
                                        max_iter, info, plan->tiling.persistent, plan->tiling.wg_waves,
                                        static_cast<hipStream_t>(stream));
     return check_hip(e, "factor/solve launch");
@@ -455,7 +455,7 @@ panel_status panel_solve_noalloc(const panel_plan *plan, const double *xy, const
             ? launch_assemble_hs(v, plan->B, plan->max_ld, mixed, xy, alpha, chord, vinf, s)
             : launch_assemble(v, plan->B, plan->max_cols, mixed, xy, alpha, chord, vinf, s);
     if (e != hipSuccess) return check_hip(e, "assembly launch");
-    e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, mixed, refine_tol, max_iter, info,
+    e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, plan->max_k, mixed, refine_tol, max_iter, info,
                             plan->tiling.persistent, plan->tiling.wg_waves, s);
     if (e != hipSuccess) return check_hip(e, "factor/solve launch");
     e = plan->formulation == PANEL_HESS_SMITH ? launch_forces_hs(v, plan->B, plan->max_k, gamma, cp, cl, cl_p, s)

@@ -1,5 +1,21 @@
 // refine_block_impl.hpp -- one workgroup refines one airfoil's FP32 solutions
 // against the FP64 system (device functions only).
+//
+// Iterative refinement of X with the FP64 system in A64 and the FP32 factors
+// in A32.  One sweep: r = b - A x in FP64; for each right-hand side not yet
+// converged: stop if r is at the FP64 backward-error floor, ||r||_inf <=
+// sqrt(n) eps ||A||_inf ||x||_inf (no further sweep can improve x); otherwise
+// d = U^{-1} L^{-1} P r in FP32, x += d, and stop by the rule of
+// refined_enough.
+//
+// A sweep is bound by reading A64 and the factors, so up to KG right-hand
+// sides share one read of each.  Both the residual and the off-diagonal part
+// of the triangular solves run on the matrix cores as D = X^T A^T (source A a
+// 16 (right-hand sides) x 4 slice of the solutions, source B four columns of
+// 16 consecutive rows): one load of the matrix feeds all the right-hand sides
+// and costs one instruction.  (With a row per thread on the vector ALUs, four
+// right-hand sides per pass were the most that fitted in registers: 256
+// systems of order 1025 with eight right-hand sides took 4.7 ms.)
 #pragma once
 
 #include "lu_wave_impl.hpp"
@@ -8,167 +24,350 @@
 
 namespace panel {
 namespace {
+namespace rfb {
 
+using wv::TileMap;
+using wv::mfma_t;
 using wv::opaque_s;
 
 constexpr int SB = 64;     // rows per diagonal block in the triangular solves
-constexpr int JR = 16;     // columns per round trip in the refinement residual
 
-// ---- triangular solves on NR vectors at once (the refinement) -----------------
-// The matrix stays in global memory; every 64x64 diagonal block and every row of the matrix is
-// read once for all NR right-hand sides: y[r] (r < NR) are LDS vectors of
-// stride ys.  The serial chain of a diagonal block (64 broadcast steps) is
-// shared by the NR vectors.
-template <int NR>
-__device__ __forceinline__ void block_dot_n(const float *p, int ld, const float *yb, int ys, float (&s)[NR]) {
-    // one running address (a column step per load): precomputed addresses
-    // for all 64 columns would hold 128 registers
-    const size_t step = (size_t)opaque_s(ld);
-#pragma unroll 1
-    for (int j0 = 0; j0 < SB; j0 += 16) {
-        float a[16];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            a[jj] = *p;
-            p += step;
-            asm volatile("" : "+v"(p));   // keep the walk sequential (no table of offsets)
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) s[r] -= a[jj] * yb[r * ys + j0 + jj];
-            if ((jj & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-    }
+// Barrier for exchanges through LDS: global loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Maximum over each row of 16 lanes, in all its lanes.
+__device__ __forceinline__ double row16_max(double v) {
+    v = fmax(v, dpp_d<0xB1>(v));    // quad_perm [1,0,3,2]
+    v = fmax(v, dpp_d<0x4E>(v));    // quad_perm [2,3,0,1]
+    v = fmax(v, dpp_d<0x141>(v));   // row_half_mirror
+    return fmax(v, dpp_d<0x140>(v));   // row_mirror
 }
 
-template <int NR, int TB>
-__device__ __forceinline__ void trsm_lower_unit(const float *L, int ld, int n, int nr, float *y, int ys, float *sblk) {
-    ld = opaque_s(ld);   // address arithmetic formed here, not hoisted to the kernel entry
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nblk = (n + SB - 1) / SB;
-    for (int blk = 0; blk < nblk; ++blk) {
-        const int rb = blk * SB, w = min(SB, n - rb);
-        for (int idx = tid; idx < SB * SB; idx += TB) {
-            const int c = idx >> 6, r = idx & 63;
-            sblk[idx] = (c < w && r < w && r > c) ? L[(size_t)(rb + c) * ld + rb + r] : 0.0f;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            float yi[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) yi[r] = (r < nr && lane < w) ? y[r * ys + rb + lane] : 0.0f;
-#pragma unroll 2
-            for (int j = 0; j < w; ++j) {
-                const float lj = sblk[j * SB + lane];
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const float xj = readlane_t(yi[r], j);
-                    if (lane > j) yi[r] -= lj * xj;
+// perm[i] = row of the system at position i of its factored form, from the
+// sequence of exchanges; all threads call it.  Most pivots stay where they
+// are, so only the exchanges that move something are walked.
+__device__ __forceinline__ void perm_of_pivots(const int32_t *piv, int n, int tb, unsigned short *perm) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < n; i += tb) perm[i] = (unsigned short)i;
+    __syncthreads();
+    if (tid < 64) {
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int p = i0 + lane < n ? piv[i0 + lane] : i0 + lane;
+            unsigned long long m = __ballot(p != i0 + lane);
+            while (m) {
+                const int l = __ffsll((long long)m) - 1;
+                m &= m - 1;
+                const int q = __builtin_amdgcn_readlane(p, l);
+                if (lane == 0) {
+                    const unsigned short t = perm[i0 + l];
+                    perm[i0 + l] = perm[q];
+                    perm[q] = t;
                 }
             }
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r < nr && lane < w) y[r * ys + rb + lane] = yi[r];
         }
-        __syncthreads();
-        for (int row = rb + w + tid; row < n; row += TB) {
-            float acc[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r] = y[r * ys + row];
-            block_dot_n<NR>(L + (size_t)rb * ld + row, ld, y + rb, ys, acc);
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r < nr) y[r * ys + row] = acc[r];
-        }
-        __syncthreads();
     }
+    __syncthreads();
 }
 
-template <int NR, int TB>
-__device__ __forceinline__ void trsm_upper(const float *U, int ld, int n, int nr, float *y, int ys, float *sblk) {
-    ld = opaque_s(ld);   // address arithmetic formed here, not hoisted to the kernel entry
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nblk = (n + SB - 1) / SB;
-    for (int blk = nblk - 1; blk >= 0; --blk) {
-        const int rb = blk * SB, w = min(SB, n - rb);
-        for (int idx = tid; idx < SB * SB; idx += TB) {
-            const int c = idx >> 6, r = idx & 63;
-            sblk[idx] = (c < w && r <= c) ? U[(size_t)(rb + c) * ld + rb + r] : 0.0f;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            float yi[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) yi[r] = (r < nr && lane < w) ? y[r * ys + rb + lane] : 0.0f;
-            const float dinv = (lane < w) ? 1.0f / sblk[lane * SB + lane] : 0.0f;
-#pragma unroll 2
-            for (int j = w - 1; j >= 0; --j) {
-                const float uj = sblk[j * SB + lane];
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    if (lane == j) yi[r] *= dinv;
-                    const float xj = readlane_t(yi[r], j);
-                    if (lane < j) yi[r] -= uj * xj;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r < nr && lane < w) y[r * ys + rb + lane] = yi[r];
-        }
-        __syncthreads();
-        for (int row = tid; row < rb; row += TB) {
-            const float *up = U + (size_t)rb * ld + row;
-            float acc[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r] = y[r * ys + row];
-            if (w == SB) {   // every block but the last, partial one
-                block_dot_n<NR>(up, ld, y + rb, ys, acc);
-            } else {
-                for (int j = 0; j < w; ++j) {
-                    const float a = up[(size_t)j * ld];
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) acc[r] -= a * y[r * ys + rb + j];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r < nr) y[r * ys + row] = acc[r];
-        }
-        __syncthreads();
-    }
-}
-
-// Mixed precision: iterative refinement of X with the FP64 system in A64 and
-// the FP32 factors in A32.  One sweep: r = b - A x in FP64 (one pass over A
-// serving KG right-hand sides); for each right-hand side not yet converged:
-// stop if r is at the FP64 backward-error floor, ||r||_inf <= sqrt(n) eps
-// ||A||_inf ||x||_inf (no further sweep can improve x); otherwise
-// d = U^{-1} L^{-1} P r in FP32 (one pass over the factors for the group),
-// x += d, and stop by the rule of refined_enough.  KG = 4: eight would spill
-// registers in the residual pass of a 512-thread workgroup.
-constexpr int KG = 4;
-constexpr int YS = PANEL_NMAX + 1;
-template <int TB> struct WgRefLds {
-    double sx[KG][YS];   // current solutions
-    float sd[KG][YS];    // residuals in pivot order, then the corrections
-    int perm[YS];        // position i of the factored system holds row perm[i]
-    int pinv[YS];        // and row r sits at position pinv[r]
-    double red[3][KG][TB / 64];
-    float sblk[SB * SB];
+// KG: right-hand sides per pass (4 or 8); NM: largest order.
+template <int TB, int KG, int NM> struct WgRefLds {
+    static constexpr int W = TB / 64;
+    double sx[NM * KG];           // current solutions, [row][right-hand side]
+    alignas(16) float sd[NM * KG];   // residuals by pivot position, then the corrections
+    union {
+        float sblk[SB * SB];                     // a diagonal block of the factors
+        double part[W][2][64][KG / 4];           // partial sums of a residual tile
+    } u;
+    double rpart[W][32];          // partial row sums of |A|
+    double red[KG][W];
+    unsigned short perm[NM], pinv[NM];
 };
 
-// FP64 refinement of the FP32 solutions of one airfoil, KG right-hand sides
-// per pass: one read of A64 forms their residuals, one read of the FP32
-// factors their corrections.
-template <int TB>
+// Solve the diagonal block [rb, rb + w) for all right-hand sides, one or two
+// per wavefront side by side (lane = row); LOWER: unit lower, else upper.
+template <bool LOWER, int TB, int KG, typename Lds>
+__device__ __forceinline__ void diag_solve(int rb, int w, Lds &S) {
+    constexpr int W = TB / 64, NR = (KG + W - 1) / W;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (wave >= KG) return;
+    const float *sblk = S.u.sblk;
+    float y[NR];
+#pragma unroll
+    for (int m = 0; m < NR; ++m) y[m] = lane < w ? S.sd[(rb + lane) * KG + wave + W * m] : 0.0f;
+    const float dinv = LOWER ? 1.0f : lane < w ? 1.0f / sblk[lane * SB + lane] : 0.0f;
+#pragma unroll 1
+    for (int jb = 0; jb < SB; jb += 8) {
+        const int j0 = LOWER ? jb : SB - 8 - jb;
+        if (j0 >= w) continue;
+        float a[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[j] = sblk[(j0 + j) * SB + lane];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const int j = LOWER ? jj : 7 - jj;
+            if (j0 + j < w) {
+#pragma unroll
+                for (int m = 0; m < NR; ++m) {
+                    if (!LOWER && lane == j0 + j) y[m] *= dinv;
+                    const float xj = readlane_t(y[m], j0 + j);
+                    if (LOWER ? lane > j0 + j : lane < j0 + j) y[m] -= a[j] * xj;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+        if (lane < w) S.sd[(rb + lane) * KG + wave + W * m] = y[m];
+}
+
+// L y = y (unit lower) or U y = y for the KG vectors in S.sd.
+template <bool LOWER, int TB, int KG, typename Lds>
+__device__ __forceinline__ void tri_solve(const float *F, int ld, int n, Lds &S) {
+    constexpr int W = TB / 64, E = SB * SB / TB;
+    typedef TileMap<float>::acc acc_t;
+    typedef float f4_t __attribute__((ext_vector_type(4)));
+    ld = opaque_s(ld);
+    const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, k4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nblk = (n + SB - 1) / SB;
+    float db[E];   // the next diagonal block on its way to LDS
+    auto load_diag = [&](int blk) {
+        const int rb = blk * SB;
+        const int r = min(rb + lane, n - 1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) db[e] = F[(size_t)min(rb + wave + W * e, n - 1) * ld + r];
+    };
+    load_diag(LOWER ? 0 : nblk - 1);
+#pragma unroll 1
+    for (int bb = 0; bb < nblk; ++bb) {
+        const int blk = LOWER ? bb : nblk - 1 - bb;
+        const int rb = blk * SB, w = min(SB, n - rb);
+#pragma unroll
+        for (int e = 0; e < E; ++e) S.u.sblk[(wave + W * e) * SB + lane] = db[e];
+        load_diag(LOWER ? min(blk + 1, nblk - 1) : max(blk - 1, 0));
+        // rows that take this block's contribution, 32 per wavefront at a time
+        const int r0 = LOWER ? rb + SB : 0, r1 = LOWER ? n : rb;
+        float lf[2][16];
+        auto load_f = [&](int r) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int rr = max(min(r + 16 * t + i16, r1 - 1), 0);
+#pragma unroll
+                for (int s = 0; s < 16; ++s) lf[t][s] = F[(size_t)(rb + min(4 * s + k4, w - 1)) * ld + rr];
+            }
+        };
+        if (r0 + 32 * wave < r1) load_f(r0 + 32 * wave);
+        lds_barrier();
+        diag_solve<LOWER, TB, KG>(rb, w, S);
+        lds_barrier();
+        float xa[16];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const int k = 4 * s + k4;
+            xa[s] = k < w ? -S.sd[(rb + min(k, w - 1)) * KG + (i16 & (KG - 1))] : 0.0f;
+        }
+#pragma unroll 1
+        for (int r = r0 + 32 * wave; r < r1; r += 32 * W) {
+            acc_t a0[2], a1[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a0[t][e] = a1[t][e] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 16; s += 2)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    a0[t] = mfma_t(xa[s], lf[t][s], a0[t]);
+                    a1[t] = mfma_t(xa[s + 1], lf[t][s + 1], a1[t]);
+                }
+            if (r + 32 * W < r1) load_f(r + 32 * W);
+            // right-hand sides 4 k4 .. 4 k4 + 3 of row i16
+            if (4 * k4 < KG) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int rr = r + 16 * t + i16;
+                    if (rr < r1) {
+                        f4_t *c = reinterpret_cast<f4_t *>(&S.sd[rr * KG + 4 * k4]);
+                        f4_t v = *c;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] += a0[t][e] + a1[t][e];
+                        *c = v;
+                    }
+                }
+            }
+        }
+        lds_barrier();
+    }
+}
+
+// Partial residual of 32 rows over the columns [kb, ke): acc[t][e] -= sum_k
+// A[row][k] x[k][rhs] (rhs = k4 + 4 e, row = r0 + 16 t + i16), and with NORM
+// the sums of |A| over this lane's columns.
+template <int KG, bool NORM, typename Lds>
+__device__ __forceinline__ void resid_tile(const double *A, int ld, int n, int r0, int kb, int ke,
+                                           TileMap<double>::acc (&acc)[2], double (&ra)[2], Lds &S) {
+    constexpr int KS = 8;   // k-steps (of four columns) per round trip
+    const int lane = threadIdx.x & 63, i16 = lane & 15, k4 = lane >> 4;
+    const double *ap[2] = {A + min(r0 + i16, n - 1), A + min(r0 + 16 + i16, n - 1)};
+    double a[2][KS];
+    auto load_a = [&](int k0) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const size_t c = (size_t)min(k0 + 4 * s + k4, n - 1) * ld;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) a[t][s] = ap[t][c];
+        }
+    };
+    load_a(kb);
+#pragma unroll 1
+    for (int k0 = kb; k0 < ke; k0 += 4 * KS) {
+        double b[2][KS];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) b[t][s] = a[t][s];
+        load_a(k0 + 4 * KS);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k = k0 + 4 * s + k4;
+            const double x = k < ke ? -S.sx[min(k, n - 1) * KG + (i16 & (KG - 1))] : 0.0;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                acc[t] = mfma_t(x, b[t][s], acc[t]);
+                if (NORM) ra[t] += k < ke ? fabs(b[t][s]) : 0.0;
+            }
+        }
+    }
+}
+
+// Residuals of the group's solutions: to S.sd by pivot position, their sizes
+// (of right-hand side tid % KG) to m, and with NORM ||A||_inf to anrm.
+template <int TB, int KG, bool NORM, typename Lds>
+__device__ __forceinline__ void residual(const double *A, int ld, int n, int k0, int kn, double &m, double &anrm,
+                                         Lds &S) {
+    constexpr int W = TB / 64;
+    typedef TileMap<double>::acc acc_t;
+    ld = opaque_s(ld);
+    const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, k4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = (n + 31) / 32, full = nt / W * W;
+    double rmax[KG / 4], rowmax = 0.0;
+#pragma unroll
+    for (int e = 0; e < KG / 4; ++e) rmax[e] = 0.0;
+    auto start = [&](acc_t (&acc)[2], int r0, bool with_b) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc[t][e] = with_b && e < KG / 4
+                                ? A[(size_t)(n + k0 + min(k4 + 4 * e, kn - 1)) * ld + min(r0 + 16 * t + i16, n - 1)]
+                                : 0.0;
+    };
+    auto finish = [&](int row, int e, double r) {
+        S.sd[S.pinv[row] * KG + k4 + 4 * e] = (float)r;
+        rmax[e] = fmax(rmax[e], fabs(r));
+    };
+    for (int tile = wave; tile < full; tile += W) {
+        const int r0 = 32 * tile;
+        acc_t acc[2];
+        double ra[2] = {0.0, 0.0};
+        start(acc, r0, true);
+        resid_tile<KG, NORM>(A, ld, n, r0, 0, n, acc, ra, S);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row = r0 + 16 * t + i16;
+            if (row < n) {
+#pragma unroll
+                for (int e = 0; e < KG / 4; ++e) finish(row, e, acc[t][e]);
+            }
+            if (NORM) {
+                ra[t] += __shfl_xor(ra[t], 16);
+                ra[t] += __shfl_xor(ra[t], 32);
+                if (row < n) rowmax = fmax(rowmax, ra[t]);
+            }
+        }
+    }
+    // the tiles left over are split by columns over the wavefronts (a round
+    // of its own for a few rows would leave most of the workgroup idle)
+    const int kc = ((n + W - 1) / W + 3) & ~3;
+    for (int tile = full; tile < nt; ++tile) {
+        const int r0 = 32 * tile;
+        acc_t acc[2];
+        double ra[2] = {0.0, 0.0};
+        start(acc, r0, wave == 0);
+        const int kb = min(kc * wave, n), ke = min(kb + kc, n);
+        if (kb < ke) resid_tile<KG, NORM>(A, ld, n, r0, kb, ke, acc, ra, S);
+        lds_barrier();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int e = 0; e < KG / 4; ++e) S.u.part[wave][t][lane][e] = acc[t][e];
+            if (NORM) {
+                ra[t] += __shfl_xor(ra[t], 16);
+                ra[t] += __shfl_xor(ra[t], 32);
+                if (k4 == 0) S.rpart[wave][16 * t + i16] = ra[t];
+            }
+        }
+        lds_barrier();
+        if (wave < 2) {   // wavefront t sums row tile t
+            const int row = r0 + 16 * wave + i16;
+            if (row < n) {
+#pragma unroll
+                for (int e = 0; e < KG / 4; ++e) {
+                    double r = S.u.part[0][wave][lane][e];
+                    for (int w = 1; w < W; ++w) r += S.u.part[w][wave][lane][e];
+                    finish(row, e, r);
+                }
+                if (NORM) {
+                    double r = 0.0;
+                    for (int w = 0; w < W; ++w) r += S.rpart[w][16 * wave + i16];
+                    rowmax = fmax(rowmax, r);
+                }
+            }
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < KG / 4; ++e) {
+        const double r = row16_max(rmax[e]);
+        if (i16 == 0) S.red[k4 + 4 * e][wave] = r;
+    }
+    if (NORM) {
+        rowmax = wave_max(rowmax);
+        if (lane == 0) S.rpart[wave][0] = rowmax;
+    }
+    lds_barrier();
+    m = S.red[tid % KG][0];
+    for (int w = 1; w < W; ++w) m = fmax(m, S.red[tid % KG][w]);
+    if (NORM) {
+        anrm = S.rpart[0][0];
+        for (int w = 1; w < W; ++w) anrm = fmax(anrm, S.rpart[w][0]);
+    }
+    lds_barrier();
+}
+
+// Maximum over the threads of the same right-hand side (tid % KG).
+template <int TB, int KG, typename Lds>
+__device__ __forceinline__ double group_max(double x, Lds &S) {
+    constexpr int W = TB / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int off = KG; off < 64; off <<= 1) x = fmax(x, __shfl_xor(x, off));
+    if (lane < KG) S.red[lane][wave] = x;
+    lds_barrier();
+    x = S.red[tid % KG][0];
+    for (int w = 1; w < W; ++w) x = fmax(x, S.red[tid % KG][w]);
+    lds_barrier();
+    return x;
+}
+
+template <int TB, int KG, int NM>
 __device__ __forceinline__ void wg_refine(const WsView &v, int b, int32_t *__restrict__ info, double tol,
-                                          int max_iter, WgRefLds<TB> &S) {
+                                          int max_iter, WgRefLds<TB, KG, NM> &S) {
     const AirfoilMeta mt = v.meta[b];
     const int n = mt.n1, ld = mt.ld;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (info[b] != 0) {
+    const int tid = threadIdx.x;
+    if (info[b] != 0 || n > NM) {   // (n > NM: the caller's choice of instance excludes it)
         if (tid == 0) {
             v.iters[b] = 0;
             v.flag[b] = info[b];
@@ -177,155 +376,71 @@ __device__ __forceinline__ void wg_refine(const WsView &v, int b, int32_t *__res
     }
     const double *A = v.a64 + mt.a_off;
     const float *LU = v.a32 + mt.a_off;
-    const int32_t *piv = v.piv + mt.piv_off;
     double *X = v.x + mt.x_off;
-    if (tid == 0) {
-        for (int i = 0; i < n; ++i) S.perm[i] = i;
-        for (int i = 0; i < n; ++i) {
-            const int p = piv[i];
-            const int t0 = S.perm[i];
-            S.perm[i] = S.perm[p];
-            S.perm[p] = t0;
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += TB) S.pinv[S.perm[i]] = i;
-    // block-wide maxima of three values per right-hand side
-    auto bmax = [&](double (&a)[3][KG]) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int r = 0; r < KG; ++r) {
-                double x = a[q][r];
-                for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
-                if (lane == 0) S.red[q][r][wave] = x;
-            }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int r = 0; r < KG; ++r) {
-                double x = S.red[q][r][0];
-                for (int w = 1; w < TB / 64; ++w) x = fmax(x, S.red[q][r][w]);
-                a[q][r] = x;
-            }
-        __syncthreads();
-    };
+    perm_of_pivots(v.piv + mt.piv_off, n, TB, S.perm);
+    for (int i = tid; i < n; i += TB) S.pinv[S.perm[i]] = (unsigned short)i;
     const double floor_c = sqrt((double)n) * 2.220446049250313e-16;
     double anrm = -1.0;   // ||A||_inf, found during the first residual
     int worst = 0;
     bool failed = max_iter == 0;
+    const int rhs = tid % KG;   // this thread's right-hand side in elementwise passes
     for (int k0 = 0; k0 < mt.K; k0 += KG) {
         const int kn = min(KG, mt.K - k0);
-        for (int kk = 0; kk < kn; ++kk)
-            for (int i = tid; i < n; i += TB) S.sx[kk][i] = X[(size_t)(k0 + kk) * n + i];
-        __syncthreads();
-        bool conv[KG];
-        int sweeps[KG];
-        double dprev[KG];
-#pragma unroll
-        for (int kk = 0; kk < KG; ++kk) {
-            conv[kk] = kk >= kn;
-            sweeps[kk] = 0;
-            dprev[kk] = -1.0;
+        // (right-hand sides past the last repeat it and are not written back)
+        double x0 = 0.0;
+        for (int i = tid / KG; i < n; i += TB / KG) {
+            const double x = X[(size_t)(k0 + min(rhs, kn - 1)) * n + i];
+            S.sx[i * KG + rhs] = x;
+            x0 = fmax(x0, fabs(x));
         }
-        for (int it = 0; it < max_iter; ++it) {
-            bool all = true;
-#pragma unroll
-            for (int kk = 0; kk < KG; ++kk) all = all && conv[kk];
-            if (all) break;
-            // r = b - A x for the group, one pass over A; the residual goes
-            // straight to its pivot position (FP32) and its size is kept
-            double m[3][KG];
-#pragma unroll
-            for (int kk = 0; kk < KG; ++kk) m[0][kk] = m[1][kk] = m[2][kk] = 0.0;
-            double rowmax = 0.0;
-            const bool first_pass = anrm < 0.0;
-            const int ldr = opaque_s(ld);
-            for (int i = tid; i < n; i += TB) {
-                double sk[KG];
-#pragma unroll
-                for (int kk = 0; kk < KG; ++kk) sk[kk] = (kk < kn) ? A[(size_t)(n + k0 + kk) * ldr + i] : 0.0;
-                double ra = 0.0;
-                // JR columns per round trip: all their loads are issued
-                // before the first product (left to itself the compiler put
-                // a wait after every load, one memory latency per element)
-                for (int j0 = 0; j0 < n; j0 += JR) {
-                    double a[JR];
-#pragma unroll
-                    for (int jj = 0; jj < JR; ++jj) a[jj] = A[(size_t)min(j0 + jj, n - 1) * ldr + i];
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int jj = 0; jj < JR; ++jj) {
-                        if (j0 + jj < n) {
-#pragma unroll
-                            for (int kk = 0; kk < KG; ++kk)
-                                if (kk < kn) sk[kk] -= a[jj] * S.sx[kk][j0 + jj];
-                            if (first_pass) ra += fabs(a[jj]);
-                        }
-                        // keep the broadcast reads of x from being hoisted all at once
-                        if ((jj & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                const int pi = S.pinv[i];
-#pragma unroll
-                for (int kk = 0; kk < KG; ++kk) {
-                    if (kk < kn) {
-                        S.sd[kk][pi] = (float)sk[kk];
-                        m[0][kk] = fmax(m[0][kk], fabs(sk[kk]));
-                        m[1][kk] = fmax(m[1][kk], fabs(S.sx[kk][i]));
-                    }
-                }
-                rowmax = fmax(rowmax, ra);
-            }
-            m[2][0] = rowmax;
-            bmax(m);
-            if (anrm < 0.0) anrm = m[2][0];
+        __syncthreads();
+        // state of this thread's right-hand side; `conv` (bit k: right-hand
+        // side k is done) is the same in every thread
+        double xn = group_max<TB, KG>(x0, S), dprev = -1.0;
+        int sweeps = 0;
+        bool mine = rhs >= kn;
+        constexpr unsigned ALL = (1u << KG) - 1u;
+        unsigned conv = (unsigned)__ballot(mine) & ALL;
+        for (int it = 0; it < max_iter && conv != ALL; ++it) {
+            double m;
+            if (anrm < 0.0)
+                residual<TB, KG, true>(A, ld, n, k0, kn, m, anrm, S);
+            else
+                residual<TB, KG, false>(A, ld, n, k0, kn, m, anrm, S);
             // a right-hand side whose residual is at the FP64 backward-error
             // floor is done; the others take a correction
-            bool need = false;
-#pragma unroll
-            for (int kk = 0; kk < KG; ++kk) {
-                if (!conv[kk] && m[0][kk] <= floor_c * anrm * m[1][kk]) conv[kk] = true;
-                if (!conv[kk]) need = true;
-            }
-            if (!need) break;
-            trsm_lower_unit<KG, TB>(LU, ld, n, kn, &S.sd[0][0], YS, S.sblk);
-            trsm_upper<KG, TB>(LU, ld, n, kn, &S.sd[0][0], YS, S.sblk);
-            double d[3][KG];
-#pragma unroll
-            for (int kk = 0; kk < KG; ++kk) d[0][kk] = d[1][kk] = d[2][kk] = 0.0;
-            for (int i = tid; i < n; i += TB) {
-#pragma unroll
-                for (int kk = 0; kk < KG; ++kk) {
-                    if (kk < kn && !conv[kk]) {
-                        const double dd = (double)S.sd[kk][i];
-                        const double x1 = S.sx[kk][i] + dd;
-                        S.sx[kk][i] = x1;
-                        d[0][kk] = fmax(d[0][kk], fabs(dd));
-                        d[1][kk] = fmax(d[1][kk], fabs(x1));
-                    }
+            mine = mine || m <= floor_c * anrm * xn;
+            conv = (unsigned)__ballot(mine) & ALL;
+            if (conv == ALL) break;
+            tri_solve<true, TB, KG>(LU, ld, n, S);
+            tri_solve<false, TB, KG>(LU, ld, n, S);
+            double d0 = 0.0, d1 = 0.0;
+            if (!mine) {
+                for (int i = tid / KG; i < n; i += TB / KG) {
+                    const double dd = (double)S.sd[i * KG + rhs];
+                    const double x1 = S.sx[i * KG + rhs] + dd;
+                    S.sx[i * KG + rhs] = x1;
+                    d0 = fmax(d0, fabs(dd));
+                    d1 = fmax(d1, fabs(x1));
                 }
             }
-            bmax(d);
-#pragma unroll
-            for (int kk = 0; kk < KG; ++kk) {
-                if (kk < kn && !conv[kk]) {
-                    ++sweeps[kk];
-                    conv[kk] = wv::refined_enough(d[0][kk], dprev[kk], d[1][kk], tol);
-                    dprev[kk] = d[0][kk];
-                }
+            d0 = group_max<TB, KG>(d0, S);
+            d1 = group_max<TB, KG>(d1, S);
+            if (!mine) {
+                ++sweeps;
+                xn = d1;
+                mine = wv::refined_enough(d0, dprev, xn, tol);
+                dprev = d0;
             }
+            conv = (unsigned)__ballot(mine) & ALL;
         }
-#pragma unroll
-        for (int kk = 0; kk < KG; ++kk) {
-            if (!conv[kk]) failed = true;
-            worst = max(worst, sweeps[kk]);
-        }
-        for (int kk = 0; kk < kn; ++kk)
-            for (int i = tid; i < n; i += TB) X[(size_t)(k0 + kk) * n + i] = S.sx[kk][i];
+        if (conv != ALL) failed = true;
+        worst = max(worst, sweeps);
+        if (rhs < kn)
+            for (int i = tid / KG; i < n; i += TB / KG) X[(size_t)(k0 + rhs) * n + i] = S.sx[i * KG + rhs];
         __syncthreads();
     }
+    for (int off = 1; off < KG; off <<= 1) worst = max(worst, __shfl_xor(worst, off));
     if (tid == 0) {
         v.iters[b] = worst;
         if (failed) info[b] = -2;
@@ -333,5 +448,6 @@ __device__ __forceinline__ void wg_refine(const WsView &v, int b, int32_t *__res
     }
 }
 
+}  // namespace rfb
 }  // namespace
 }  // namespace panel

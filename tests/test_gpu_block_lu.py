@@ -110,3 +110,37 @@ def test_zero_column_is_reported(precision, waves):
         d = s.plan.layout(b)
         x = s.ws[d["x"]:d["x"] + 8 * n * d["K"]].view(torch.float64)
         assert bool(torch.isnan(x).all())
+
+
+@pytest.mark.parametrize("tiling", [(0, 0, 0), (0, 0, 4), (0, 0, 8), (320, 0, 0), (320, 0, 4)])
+def test_refinement_of_uneven_right_hand_sides(tiling):
+    """1 to 16 angles per airfoil through the FP64 refinement of FP32 factors:
+    groups of four and eight right-hand sides, rows left over from the tiles
+    of 32, orders on both sides of the wave limit.  The refined solution solves
+    the FP64 system to the refinement's stop rule (a correction below 1e-10 of
+    the solution), so it agrees with a direct FP64 solve to 1e-9."""
+    import torch
+
+    import paper_1511_02166_amd as P
+    N = [31, 32, 64, 95, 128, 159, 160, 200, 255, 256, 300, 319, 320, 330, 512, 540, 700, 767]
+    K = [1 + (5 * i) % 16 for i in range(len(N))]
+    K[1:4] = [2, 8, 9]
+    xy, noff = synth.joukowski_batch(11, len(N), N)
+    aoff = np.concatenate([[0], np.cumsum(K)]).astype(np.int32)
+    alpha = torch.as_tensor(np.linspace(-0.05, 0.2, aoff[-1]), device="cuda")
+    s = P.PanelSolver(noff, aoff, P.PANEL_FP32_REFINE, tiling=tiling)
+    s.assemble(torch.as_tensor(xy, device="cuda"), alpha)
+    torch.cuda.synchronize()
+    systems = [s.system(b) for b in range(len(N))]
+    s.factor_solve()
+    torch.cuda.synchronize()
+    assert np.all(s.info.cpu().numpy() == 0)
+    assert np.all(s.refine_iterations() >= 1)
+    for b, n in enumerate(np.asarray(N) + 1):
+        d = s.plan.layout(b)
+        x = s.ws[d["x"]:d["x"] + 8 * n * d["K"]].cpu().numpy().view(np.float64).reshape(d["K"], n)
+        M, R = systems[b]
+        ref = np.linalg.solve(M, R.T).T
+        err = np.max(np.abs(x - ref)) / np.max(np.abs(ref))
+        floor = 64 * 2.0 ** -53 * np.linalg.cond(M, np.inf)
+        assert err <= max(1e-9, floor), (n - 1, d["K"], err, floor)
