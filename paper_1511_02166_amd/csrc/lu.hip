@@ -41,11 +41,25 @@ bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
     return n_block <= device_cus();
 }
 
+// Systems within the wave limit by a workgroup each instead of a wavefront
+// each.  A wavefront alone on its SIMD takes as long for one system as for a
+// thousand, so below about one and a half systems of the largest order per CU
+// (FP64; three in FP32, whose matrix cores are faster) the workgroups win.
+// Factor + solve, wavefronts against workgroups: FP64, one system of order
+// 161 (nine angles) 417 -> 236 us, 256 of order 129 204 -> 187 us, of 257
+// 653 -> 441 us, 680 of 66 to 320 next to 320 larger ones 3.13 -> 1.97 ms,
+// but 512 of order 129 220 -> 237 us and 256 of order 65 84 -> 91 us; with
+// FP32 refinement, 512 of order 129 321 -> 289 us, 1024 436 -> 550 us.
+bool small_in_blocks(int32_t max_n1_small, double small_eff, int32_t mixed) {
+    if (max_n1_small <= (mixed ? 64 : 96)) return false;
+    return small_eff <= (mixed ? 3.0 : 1.5) * device_cus();
+}
+
 }  // namespace
 
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
-                               int32_t max_k, int32_t mixed, double tol, int32_t max_iter, int32_t *info,
-                               int32_t persistent, int32_t wg_waves, hipStream_t stream) {
+                               int32_t max_n1_small, double small_eff, int32_t max_k, int32_t mixed, double tol,
+                               int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream) {
     hipError_t e = hipSuccess;
     if (persistent && (n_block == 0 || !eight_waves(n_block, max_n1_block, wg_waves == 0 ? 4 : wg_waves))) {
         const int n_small = B - n_block;
@@ -53,11 +67,13 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
         return launch_lu_batch(v, grid, B, n_block, mixed, tol, max_iter, info, stream);
     }
     const int32_t waves = eight_waves(n_block, max_n1_block, wg_waves) ? 8 : 4;
-    if (n_block > 0) {
+    if (wg_waves == 0 && small_in_blocks(max_n1_small, small_eff, mixed)) {
+        // every system by a workgroup, in one launch
+        e = launch_lu_block(v, B, n_block > 0 && eight_waves(B, max_n1_block, 0) ? 8 : 4, mixed, info, stream);
+    } else {
         e = launch_lu_block(v, n_block, waves, mixed, info, stream);
-        if (e != hipSuccess) return e;
+        if (e == hipSuccess) e = launch_lu_wave(v, n_block, B - n_block, mixed, info, stream);
     }
-    e = launch_lu_wave(v, n_block, B - n_block, mixed, info, stream);
     if (e != hipSuccess) return e;
     if (mixed) {
         e = launch_refine_block(v, 0, n_block, 1, max_n1_block, max_k, waves, info, tol, max_iter, stream);

@@ -104,9 +104,9 @@ constexpr int PANEL_WAVE_MAX_N1 = 64 * PANEL_WAVE_RMAX;
 // every workgroup-kernel system fits four wavefronts (n1 <= 768) and
 // wg_waves != 8.  wg_waves: 4 or 8 wavefronts per workgroup-kernel system,
 // 0 = eight when the batch has at most one airfoil per CU.
-hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block, int32_t max_k,
-                               int32_t mixed, double tol, int32_t max_iter, int32_t *info,
-                               int32_t persistent, int32_t wg_waves, hipStream_t stream);
+hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
+                               int32_t max_n1_small, double small_eff, int32_t max_k, int32_t mixed, double tol,
+                               int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream);
 hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t mixed, int32_t *info,
                           hipStream_t stream);
 // (airfoils with more than kmax right-hand sides are left to another kernel)
