@@ -11,11 +11,8 @@
 #include "panel_internal.hpp"
 
 namespace panel {
-namespace {
 
-constexpr int TPB = 256;   // threads per workgroup by default (4 wavefronts)
-
-// Compute units of the current device (read once per process and device).
+// Compute units of the current device.
 int device_cus() {
     static int cus[64] = {0};
     int dev = 0;
@@ -27,6 +24,10 @@ int device_cus() {
     }
     return cus[dev];
 }
+
+namespace {
+
+constexpr int TPB = 256;   // threads per workgroup by default (4 wavefronts)
 
 // Eight wavefronts per airfoil for the workgroup kernels: by default when
 // the batch has at most one airfoil per CU (measured: 256 sections at

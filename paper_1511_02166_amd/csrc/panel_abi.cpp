@@ -423,8 +423,8 @@ panel_status panel_adjoint(const panel_plan *plan, const void *ws, const double 
     WsView v = ws_view(const_cast<void *>(ws), plan->layout);
     const int32_t mixed = plan->precision == PANEL_FP32_REFINE;
     hipError_t e = plan->formulation == PANEL_HESS_SMITH
-                       ? launch_adjoint_hs(v, plan->B, mixed, xy, dcl, dcp, dxy, info, static_cast<hipStream_t>(stream))
-                       : launch_adjoint(v, plan->B, plan->n_block, plan->max_k, mixed, xy, dcl, dcp, dxy, info,
+                       ? launch_adjoint_hs(v, plan->B, plan->max_n1, mixed, xy, dcl, dcp, dxy, info, static_cast<hipStream_t>(stream))
+                       : launch_adjoint(v, plan->B, plan->n_block, plan->max_n1_block, plan->max_n1_small, plan->max_k, mixed, xy, dcl, dcp, dxy, info,
                                         static_cast<hipStream_t>(stream));
     return check_hip(e, "adjoint launch");
 }

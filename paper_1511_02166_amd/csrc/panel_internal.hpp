@@ -85,6 +85,9 @@ inline __host__ __device__ WsView ws_view(void *ws, const WsLayout &l) {
     return v;
 }
 
+// Compute units of the current device (read once per process and device).
+int device_cus();
+
 // Kernel launchers (each enqueues on `stream`, returns hipGetLastError()).
 hipError_t launch_naca4(int32_t B, const int32_t *node_off, int32_t closed_te, const double *mpt,
                         double *xy, hipStream_t stream);
@@ -139,16 +142,16 @@ hipError_t launch_math_eval(int32_t n, const double *x, const double *y, double 
                             hipStream_t stream);
 // ka < 0: one pass with cl cotangents for all angles; ka >= 0: angle ka
 // only, with its cl and (dcp non-NULL) cp cotangents, added to dxy for ka > 0.
-hipError_t launch_adjoint(const WsView &v, int32_t B, int32_t n_block, int32_t max_k, int32_t mixed,
-                          const double *xy, const double *dcl, const double *dcp, double *dxy, int32_t *info,
-                          hipStream_t stream);
+hipError_t launch_adjoint(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block, int32_t max_n1_small,
+                          int32_t max_k, int32_t mixed, const double *xy, const double *dcl, const double *dcp, double *dxy,
+                          int32_t *info, hipStream_t stream);
 hipError_t launch_adjoint_wave(const WsView &v, int32_t first, int32_t count, int32_t mixed, const double *xy,
                                const double *dcl, const double *dcp, int32_t ka, double *dxy, int32_t *info,
                                hipStream_t stream);
 // Hess-Smith formulation: one workgroup per airfoil, all angles, cl and (dcp
 // non-NULL) cp cotangents.
-hipError_t launch_adjoint_hs(const WsView &v, int32_t B, int32_t mixed, const double *xy, const double *dcl,
-                             const double *dcp, double *dxy, int32_t *info, hipStream_t stream);
+hipError_t launch_adjoint_hs(const WsView &v, int32_t B, int32_t max_n1, int32_t mixed, const double *xy,
+                             const double *dcl, const double *dcp, double *dxy, int32_t *info, hipStream_t stream);
 
 // Genetic algorithm (ga.hip).  Small tables travel by value as kernel
 // arguments.
