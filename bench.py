@@ -39,17 +39,16 @@ METRIC = "airfoil solves/s at N=256 (FP64 vs FP32+refine) + Cl err vs FP64 oracl
 PEAK = {"f64": 78.6e12, "f32": 157.3e12, "hbm": 8.0e12}
 
 # FP64 operations per off-diagonal influence entry of the assembly kernel,
-# counted from its compiled gfx950 code: one logarithm (27 FP64 instructions,
-# 17 of them FMA), one arctangent (34, 15 FMA) and the closed-form
-# combination; 39 FMA x 2 + 40 other FP64 instructions in total.
-ASM_FLOPS_PER_ENTRY = 118.0
+# counted from its compiled gfx950 code (the interior loop, two entries per
+# trip): one logarithm, one arctangent and the closed-form combination; 31
+# FMA x 2 + 35 other FP64 instructions.
+ASM_FLOPS_PER_ENTRY = 97.0
 
-# FP64 operations per (control point, panel) pair of the adjoint's pair
-# pass, counted from its compiled gfx950 loop as the difference between
-# builds with five and four control-point slots per lane: 52 FMA x 2 + 63
-# other FP64 instructions (the logarithm, the arctangent and the derivative
-# algebra of the panel integral).
-ADJ_FLOPS_PER_PAIR = 167.0
+# FP64 operations per (control point, panel) pair of the adjoint's pair loop,
+# counted from its compiled gfx950 code: 59 FMA x 2 + 76 other FP64
+# instructions (the logarithm, the arctangent, the derivative algebra of the
+# panel integral, the sums over the wavefront).
+ADJ_FLOPS_PER_PAIR = 194.0
 
 # HBM bytes moved by one launch of the FP64 LU kernel on the 2048 x N=256
 # batch, from rocprofv3 FETCH_SIZE / WRITE_SIZE scaled by a plain copy's

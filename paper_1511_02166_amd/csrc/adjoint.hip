@@ -57,6 +57,7 @@ template <typename T, int TB, int NM> struct AdjLds {
     };
     LambdaLds<T, NM> lx;
     double red[3][TB / 64];
+    double at[fm::kAtanTab];
     unsigned short perm[NM];
 };
 
@@ -99,6 +100,7 @@ __global__ __launch_bounds__(TB, TB >= 512 ? 4 : 3) void adjoint_kernel(WsView v
         return;
     }
     __shared__ AdjLds<T, TB, NM> S;
+    load_atan_table(S.at);
     const double *P = xy + 2 * (size_t)mt.node_off;
     for (int k = tid; k <= N; k += TB) {
         S.sx[k] = P[2 * k];
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(TB, TB >= 512 ? 4 : 3) void adjoint_kernel(WsView v
                 const double e2x = mx - Bx, e2y = my - By;
                 const double l2 = plog(e2x * e2x + e2y * e2y);
                 const double cr = d1x * e2y - d1y * e2x;
-                const double th = patan2(cr, d1x * e2x + d1y * e2y);
+                const double th = patan2(cr, d1x * e2x + d1y * e2y, S.at);
                 const double hl = 0.5 * (l1 - l2);
                 const double xi = d1x * tx + d1y * ty, eta = d1x * nx + d1y * ny;
                 const double G = -kInv4Pi * iL *

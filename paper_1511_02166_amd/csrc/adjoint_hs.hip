@@ -56,6 +56,7 @@ template <typename T, int TB, int NM> struct HsLds {
     };
     LambdaLds<T, NM> lx;
     double red[3][TB / 64];
+    double at[fm::kAtanTab];
     unsigned short perm[NM];
 };
 
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(TB) void adjoint_hs_kernel(WsView v, const double *
         return;
     }
     __shared__ HsLds<T, TB, NM> S;
+    load_atan_table(S.at);
     const double *P = xy + 2 * (size_t)mt.node_off;
     for (int k = tid; k <= N; k += TB) {
         S.sx[k] = P[2 * k];
@@ -223,7 +225,7 @@ __global__ __launch_bounds__(TB) void adjoint_hs_kernel(WsView v, const double *
                     ax += (aa * d1x - bb * d1y) * r1 - (aa * d2x - bb * d2y) * r2;
                     ay += (aa * d1y + bb * d1x) * r1 - (aa * d2y + bb * d2x) * r2;
                     const double cr = d1x * d2y - d1y * d2x, dd = d1x * d2x + d1y * d2y;
-                    const double beta = patan2(-cr, dd), lg = 0.5 * (l1 - l2);
+                    const double beta = patan2(-cr, dd, S.at), lg = 0.5 * (l1 - l2);
                     phi += lg * bb - beta * aa;
                 }
                 d1x = d2x;
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(TB) void adjoint_hs_kernel(WsView v, const double *
                     const double d2x = mx - qx, d2y = my - qy;
                     const double q2 = d2x * d2x + d2y * d2y;
                     const double cr = dx * d2y - dy * d2x, dd = dx * d2x + dy * d2y;
-                    const double beta = patan2(-cr, dd), lg = 0.5 * (plog(q) - plog(q2));
+                    const double beta = patan2(-cr, dd, S.at), lg = 0.5 * (plog(q) - plog(q2));
                     cphi += lg * bb - beta * aa;
                 }
                 if (has_e && j != nd - 1) {   // node nd is P_{i+1} of panel i = nd - 1: -d/dd2

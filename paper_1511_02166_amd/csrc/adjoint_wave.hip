@@ -145,6 +145,8 @@ __global__ __launch_bounds__(WL, 2) void adjoint_wave_kernel(WsView v, int32_t f
     __shared__ double xbar[NW], lam[NW], wv[NW], tmp[NW];
     __shared__ double ox[NW + 1], oy[NW + 1];
     __shared__ int perm[NW];
+    __shared__ double s_at[fm::kAtanTab];
+    load_atan_table(s_at);
     __shared__ float yf[sizeof(T) == 4 ? NW : 1];
 
     const double *P = xy + 2 * (size_t)mt.node_off;
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(WL, 2) void adjoint_wave_kernel(WsView v, int32_t f
             const double e2x = mx[q] - Bx, e2y = my[q] - By;
             const double l2 = plog(e2x * e2x + e2y * e2y);
             const double cr = d1x[q] * e2y - d1y[q] * e2x;
-            const double th = patan2(cr, d1x[q] * e2x + d1y[q] * e2y);
+            const double th = patan2(cr, d1x[q] * e2x + d1y[q] * e2y, s_at);
             const double hl = 0.5 * (l1[q] - l2);
             const double xi = d1x[q] * tx + d1y[q] * ty, eta = d1x[q] * nx + d1y[q] * ny;
             const double G = -kInv4Pi * iL *

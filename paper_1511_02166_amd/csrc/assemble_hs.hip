@@ -45,7 +45,7 @@ constexpr int HS_TPB = 256;
 template <bool MIXED>
 __device__ void hs_kutta_row(const WsView &v, const AirfoilMeta &mt, const double *sx, const double *sy,
                              const double *stx, const double *sty, const double *sca, const double *ssa,
-                             double vinf) {
+                             double vinf, const double *s_at) {
     const int N = mt.N, n1 = mt.n1, K = mt.K, ld = mt.ld;
     double *A = v.a64 + mt.a_off;
     float *A32 = MIXED ? v.a32 + mt.a_off : nullptr;
@@ -58,7 +58,7 @@ __device__ void hs_kutta_row(const WsView &v, const AirfoilMeta &mt, const doubl
             const int j = side == 0 ? 0 : N - 1;
             const double mx = 0.5 * (sx[j] + sx[j + 1]), my = 0.5 * (sy[j] + sy[j + 1]);
             const double d1x = mx - sx[i], d1y = my - sy[i], d2x = mx - sx[i + 1], d2y = my - sy[i + 1];
-            double beta = patan2(-(d1x * d2y - d1y * d2x), d1x * d2x + d1y * d2y);
+            double beta = patan2(-(d1x * d2y - d1y * d2x), d1x * d2x + d1y * d2y, s_at);
             double lg = 0.5 * (plog(d1x * d1x + d1y * d1y) - plog(d2x * d2x + d2y * d2y));
             if (i == j) {
                 beta = kPi;
@@ -104,6 +104,8 @@ __global__ __launch_bounds__(HS_TPB) void assemble_hs_kernel(WsView v, const dou
     __shared__ double stx[PANEL_NMAX], sty[PANEL_NMAX];
     __shared__ double sca[PANEL_KMAX], ssa[PANEL_KMAX];
     __shared__ int sbad;
+    __shared__ double s_at[fm::kAtanTab];
+    load_atan_table(s_at);
     const double *P = xy + 2 * (size_t)mt.node_off;
     if (threadIdx.x == 0) sbad = 0;
     for (int k = threadIdx.x; k <= N; k += blockDim.x) {
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(HS_TPB) void assemble_hs_kernel(WsView v, const dou
     if (bad) atomicOr(&sbad, 1);
     if (kutta) {
         __syncthreads();
-        hs_kutta_row<MIXED>(v, mt, sx, sy, stx, sty, sca, ssa, vinf);
+        hs_kutta_row<MIXED>(v, mt, sx, sy, stx, sty, sca, ssa, vinf, s_at);
         return;
     }
     if (blockIdx.y == 0) {
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(HS_TPB) void assemble_hs_kernel(WsView v, const dou
         const double cr = d1x * d2y - d1y * d2x, dd = d1x * d2x + d1y * d2y;
         // the panel frame (t, n) is left-handed: the subtended angle is minus
         // the global angle from d1 to d2
-        double beta = patan2(-cr, dd);
+        double beta = patan2(-cr, dd, s_at);
         double lg = 0.5 * (l1 - l2);
         if (i == j) {
             beta = kPi;

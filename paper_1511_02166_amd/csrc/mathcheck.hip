@@ -8,11 +8,14 @@ namespace {
 
 __global__ void math_eval_kernel(int n, const double *__restrict__ x, const double *__restrict__ y,
                                  double *__restrict__ lg, double *__restrict__ at) {
+    __shared__ double s_at[fm::kAtanTab];
+    load_atan_table(s_at);
+    __syncthreads();
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double xi = x[i];
     if (lg) lg[i] = plog(xi);
-    if (at) at[i] = patan2(y[i], xi);
+    if (at) at[i] = patan2(y[i], xi, s_at);
 }
 
 }  // namespace
