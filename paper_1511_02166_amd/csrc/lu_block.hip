@@ -5,31 +5,43 @@
 namespace panel {
 namespace {
 
-// RMAX: largest number of rows per thread in a panel (n1 <= TB * RMAX).  With
-// 256 threads two workgroups share a CU; 512 threads take the whole CU.
-template <typename T, int RMAX, int TB>
+// RMAX: largest number of rows per thread in a panel (n1 <= TB * RMAX); NTM:
+// column tiles per wavefront in the trailing update; H: 64-column halves of a
+// super-panel.
+template <typename T, int RMAX, int TB, int NTM, int H>
 __global__ __launch_bounds__(TB, 2) void lu_kernel(WsView v, int32_t *__restrict__ info_out) {
-    __shared__ blk::BlkLds<T, TB> S;
-    blk::blk_lu<T, TB, RMAX>(v, v.order[blockIdx.x], info_out, S);
+    __shared__ blk::BlkLds<T, TB, H> S;
+    blk::blk_lu<T, TB, RMAX, NTM, H>(v, v.order[blockIdx.x], info_out, S);
 }
 
 template <typename T>
-void launch_lu(const WsView &v, int32_t count, int32_t waves, int32_t *info, hipStream_t s) {
-    if (waves == 8)
-        lu_kernel<T, 3, 512><<<count, 512, 0, s>>>(v, info);   // n1 <= 1536
+void launch(const WsView &v, int32_t count, int32_t waves, int32_t max_n1, int32_t *info, hipStream_t s) {
+    constexpr int NTM = sizeof(T) == 8 ? 3 : 4;
+    // Above 768 rows the trailing blocks' traffic counts: a rank-128 update
+    // halves it (256 systems of order 1025, eight angles: 8.0 -> 7.5 ms in
+    // FP64, 4.8 -> 4.6 ms in FP32); below, its longer band solves cost more
+    // (256 of order 513: 1.50 -> 1.64 ms).  Up to 512 rows an instance of two
+    // row slots spills less than one of three (1024 of order 401 in FP64:
+    // 2.85 -> 2.70 ms).
+    if (waves == 8 && max_n1 > 768)
+        lu_kernel<T, 3, 512, sizeof(T) == 8 ? 2 : 4, 2><<<count, 512, 0, s>>>(v, info);   // n1 <= 1536
+    else if (waves == 8)
+        lu_kernel<T, 2, 512, NTM, 1><<<count, 512, 0, s>>>(v, info);   // n1 <= 1024
+    else if (max_n1 > 512)
+        lu_kernel<T, 3, 256, NTM, 1><<<count, 256, 0, s>>>(v, info);   // n1 <= 768
     else
-        lu_kernel<T, 3, 256><<<count, 256, 0, s>>>(v, info);   // n1 <= 768
+        lu_kernel<T, 2, 256, NTM, 1><<<count, 256, 0, s>>>(v, info);   // n1 <= 512
 }
 
 }  // namespace
 
-hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_t mixed, int32_t *info,
+hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_t max_n1, int32_t mixed, int32_t *info,
                            hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     if (mixed)
-        launch_lu<float>(v, count, waves, info, stream);
+        launch<float>(v, count, waves, max_n1, info, stream);
     else
-        launch_lu<double>(v, count, waves, info, stream);
+        launch<double>(v, count, waves, max_n1, info, stream);
     return hipGetLastError();
 }
 

@@ -7,8 +7,8 @@
 // when there are thousands of small systems; a large system, or a small
 // batch, needs the whole workgroup on one system.
 //
-// Algorithm (right-looking by super-panels of 64 columns, LAPACK getrf
-// semantics):
+// Algorithm (right-looking by super-panels of 64 columns, or of two halves of
+// 64 whose update of the rest is one of rank 128; LAPACK getrf semantics):
 //   * a pivot panel of NB = 16 columns sits in registers, one row per thread
 //     (row k0 + tid + TB q in slot q).  Before it is factored it takes the
 //     rank-16p update from the super-panel's p panels to its left on the
@@ -33,13 +33,13 @@
 // The K right-hand sides ride along; the back substitution solves all of
 // them in one pass over U.
 //
-// What bounds it: 256 systems of order 1025 (one per CU) spend 5.6 of 8.1 ms in
-// the trailing update, at about 4.4 TB/s of C tiles and L; smaller systems
-// wait in the pivot chain (about 1600 cycles per column).  Measured against a
-// version with a thread per column for the triangular solves, U staged in LDS
-// and one right-hand side per back substitution: 14.9 -> 8.1 ms (256 x 1025,
-// FP64, eight right-hand sides), 8.6 -> 6.3 ms in FP32, 2.80 -> 1.5 ms (320
-// systems of 322 to 451, FP64).
+// What bounds it: 256 systems of order 1025 (one per CU) spend two thirds of
+// their time in the trailing update, at about half the FP64 matrix rate;
+// smaller systems wait in the pivot chain (about 1600 cycles per column).
+// Measured against a version with a thread per column for the triangular
+// solves, U staged in LDS and one right-hand side per back substitution: 14.9
+// -> 7.5 ms (256 x 1025, FP64, eight right-hand sides), 8.6 -> 4.6 ms in FP32,
+// 7.6 -> 4.35 ms (1980 systems of 321 to 513, FP32).
 #pragma once
 
 #include <climits>
@@ -110,11 +110,12 @@ template <typename T> __device__ __forceinline__ int frag_at(int r, int k) {
 }
 __device__ __forceinline__ constexpr int pair_at(int i2, int i) { return i2 * (i2 + 1) / 2 + i; }
 
-template <typename T, int TB> struct BlkLds {
-    static constexpr int W = TB / 64;
+// H: 64-column halves of a super-panel (1 or 2).
+template <typename T, int TB, int H = 1> struct BlkLds {
+    static constexpr int W = TB / 64, NBT = NBK * H;
     // the super-panel's band in fragment order: inverses of the unit-lower
     // diagonal blocks and the blocks of L below them
-    alignas(16) T band[NBK * (NBK + 1) / 2][4 * 64];
+    alignas(16) T band[NBT * (NBT + 1) / 2][4 * 64];
     alignas(16) T crow[2][W][NB];     // each wavefront's candidate row (double-buffered)
     unsigned ckey[2][W];              // and its prefix (0: none),
     T cval[2][W];                     // magnitude
@@ -124,15 +125,15 @@ template <typename T, int TB> struct BlkLds {
     int ipiv[NB];
     union U {
         T st[W][NB][64];                                  // panel rows in transit (per wavefront)
-        alignas(16) T tile[2][RGM][16 * BSP];             // L tiles of the trailing update
+        alignas(16) T tile[2][RGM][16 * BSP * H];             // L tiles of the trailing update
         struct { T sblk[64 * 64]; T xs[64][NB + 1]; } bs;  // back substitution
     } u;
 };
 
 // ---- one column step of the panel factorisation (C is compile-time) --------
-template <typename T, int R, int C, int TB>
+template <typename T, int R, int C, int TB, typename Lds>
 __device__ __forceinline__ void blk_col(T (&p)[R][NB], int (&pos)[R], unsigned &live, int k0, int &info,
-                                        BlkLds<T, TB> &S) {
+                                        Lds &S) {
     constexpr int buf = C & 1, W = TB / 64;
     constexpr int VW = 16 / (int)sizeof(T), V0 = C / VW;   // 16-byte pieces of a row from the one that holds C
     typedef T vec_t __attribute__((ext_vector_type(VW)));
@@ -249,9 +250,9 @@ __device__ __forceinline__ void blk_col(T (&p)[R][NB], int (&pos)[R], unsigned &
     }
 }
 
-template <typename T, int R, int C, int TB>
+template <typename T, int R, int C, int TB, typename Lds>
 __device__ __forceinline__ void blk_cols(T (&p)[R][NB], int (&pos)[R], unsigned &live, int k0, int nb, int &info,
-                                         BlkLds<T, TB> &S) {
+                                         Lds &S) {
     if constexpr (C < NB) {
         if (C < nb) {
             blk_col<T, R, C, TB>(p, pos, live, k0, info, S);
@@ -262,9 +263,9 @@ __device__ __forceinline__ void blk_cols(T (&p)[R][NB], int (&pos)[R], unsigned 
 
 // Solve one column block's band in registers: f[4 i + e] holds the band's
 // block i in B-operand order (lane l: row 4 e + l/16 of block i, column
-// l%16), blocks i < nblk: X_i = linv_i Y_i, then Y_j -= L_ji X_i.
+// l%16), blocks i < nblk (the band's from i0 on): X_i = linv_i Y_i, then Y_j -= L_ji X_i.
 template <typename T, int NT, int NBLK>
-__device__ __forceinline__ void band_solve(T (&uf)[NT][4 * NBLK], int nblk, const T (*band)[4 * 64]) {
+__device__ __forceinline__ void band_solve(T (&uf)[NT][4 * NBLK], int nblk, int i0, const T (*band)[4 * 64]) {
     typedef typename TileMap<T>::acc acc_t;
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -272,7 +273,7 @@ __device__ __forceinline__ void band_solve(T (&uf)[NT][4 * NBLK], int nblk, cons
         if (i < nblk) {
             T li[4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) li[s] = band[pair_at(i, i)][4 * lane + s];
+            for (int s = 0; s < 4; ++s) li[s] = band[pair_at(i0 + i, i0 + i)][4 * lane + s];
             T xn[NT][4];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
@@ -293,7 +294,7 @@ __device__ __forceinline__ void band_solve(T (&uf)[NT][4 * NBLK], int nblk, cons
                 if (j < nblk) {
                     T lb[4];
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) lb[s] = band[pair_at(j, i)][4 * lane + s];
+                    for (int s = 0; s < 4; ++s) lb[s] = band[pair_at(i0 + j, i0 + i)][4 * lane + s];
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         acc_t acc;
@@ -315,9 +316,9 @@ __device__ __forceinline__ void band_solve(T (&uf)[NT][4 * NBLK], int nblk, cons
 // A[k0:n, panel] -= L[k0:n, K0:k0] U, U = L_band^{-1} A[K0:k0, panel].  Every
 // wavefront forms U for itself (no exchange to wait for); the first one
 // writes it back, once all have read the band.
-template <typename T, int R, int TB>
-__device__ __forceinline__ void blk_load(T (&p)[R][NB], T *A, int ld, int n, int K0, int k0, int nb, int np,
-                                         BlkLds<T, TB> &S) {
+template <typename T, int R, int TB, typename Lds>
+__device__ __forceinline__ void blk_load(T (&p)[R][NB], T *A, int ld, int n, int K0, int k0, int nb, int np, int i0,
+                                         Lds &S) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (np == 0) {
         // every load is issued (clamped addresses) before any is masked
@@ -342,7 +343,7 @@ __device__ __forceinline__ void blk_load(T (&p)[R][NB], T *A, int ld, int n, int
 #pragma unroll
             for (int e = 0; e < 4; ++e) uf[0][4 * i + e] = up[16 * i + 4 * e];
         }
-    band_solve<T, 1, PM>(uf, np, S.band);
+    band_solve<T, 1, PM>(uf, np, i0, S.band);
     lds_barrier();   // every wavefront has read the band (its solve used the loads)
     if (wave == 0 && i16 < nb) {
 #pragma unroll
@@ -408,14 +409,14 @@ __device__ __forceinline__ void blk_load(T (&p)[R][NB], T *A, int ld, int n, int
 }
 
 // ---- one pivot panel: load and update, factorise, store ---------------------
-template <typename T, int R, int TB>
-__device__ __forceinline__ void blk_panel(T *A, int ld, int n, int K0, int k0, int nb, int32_t *piv, int &info,
-                                          BlkLds<T, TB> &S) {
+template <typename T, int R, int TB, typename Lds>
+__device__ __forceinline__ void blk_panel(T *A, int ld, int n, int K0, int k0, int nb, int i0, int32_t *piv, int &info,
+                                          Lds &S) {
     ld = opaque_s(ld);
     const int tid = threadIdx.x;
     T p[R][NB];
     const int np = (k0 - K0) / NB;
-    blk_load<T, R, TB>(p, A, ld, n, K0, k0, nb, np, S);
+    blk_load<T, R, TB>(p, A, ld, n, K0, k0, nb, np, i0, S);
     int pos[R];
     unsigned live = 0;
 #pragma unroll
@@ -464,8 +465,8 @@ __device__ __forceinline__ void blk_panel(T *A, int ld, int n, int K0, int k0, i
 
 // The panel's row moves on every column outside it, a column per thread: all
 // of a column's loads are issued together, moves past nmv repeat the last.
-template <typename T, int M, int TB>
-__device__ __forceinline__ void blk_moves_m(T *A, int ld, int ncols, int k0, int nb, int nmv, BlkLds<T, TB> &S) {
+template <typename T, int M, int TB, typename Lds>
+__device__ __forceinline__ void blk_moves_m(T *A, int ld, int ncols, int k0, int nb, int nmv, Lds &S) {
     int src[M], dst[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
@@ -486,8 +487,8 @@ __device__ __forceinline__ void blk_moves_m(T *A, int ld, int ncols, int k0, int
     }
 }
 
-template <typename T, int TB>
-__device__ __forceinline__ void blk_moves(T *A, int ld, int ncols, int k0, int nb, BlkLds<T, TB> &S) {
+template <typename T, int TB, typename Lds>
+__device__ __forceinline__ void blk_moves(T *A, int ld, int ncols, int k0, int nb, Lds &S) {
     const int nmv = __builtin_amdgcn_readfirstlane(S.nmv);
     if (nmv == 0) return;
     ld = opaque_s(ld);
@@ -502,8 +503,8 @@ __device__ __forceinline__ void blk_moves(T *A, int ld, int ncols, int k0, int n
 // Inverse of the panel's unit-lower diagonal block, into the band (one
 // wavefront; lane j < 16 solves L x = e_j; each column of L is read from LDS
 // while the one before it is used).
-template <typename T, int TB>
-__device__ __forceinline__ void blk_linv(int i, BlkLds<T, TB> &S) {
+template <typename T, int TB, typename Lds>
+__device__ __forceinline__ void blk_linv(int i, Lds &S) {
     constexpr int VW = 16 / (int)sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(VW)));
     const int lane = threadIdx.x & 63;
@@ -536,12 +537,12 @@ __device__ __forceinline__ void blk_linv(int i, BlkLds<T, TB> &S) {
 // (columns up to c1); RG row groups of wavefronts share each column group.
 //   U  = L_band^{-1} A[band, columns]          (band: nblk 16-row blocks at kb)
 //   A[kend:n, columns] -= A[kend:n, band] U    (kend < n: the band is full)
-template <typename T, int TB, int NT, int RG>
+template <typename T, int TB, int NT, int RG, int NBLK, typename Lds>
 __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend, int cs0, int c1, int nblk,
-                                          BlkLds<T, TB> &S) {
-    constexpr int W = TB / 64, WC = W / RG, S4 = 4 * NBK;
+                                          Lds &S) {
+    constexpr int W = TB / 64, WC = W / RG, S4 = 4 * NBLK;
     constexpr int VW = 16 / (int)sizeof(T);      // k-steps per 16-byte LDS read
-    constexpr int E = RG * 16 * BSP / TB;        // staged elements per thread
+    constexpr int E = RG * 16 * 16 * NBLK / TB;        // staged elements per thread
     typedef typename TileMap<T>::acc acc_t;
     typedef T vec_t __attribute__((ext_vector_type(VW)));
     ld = opaque_s(ld);
@@ -558,7 +559,7 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
 #pragma unroll
             for (int s = 0; s < S4; ++s) uf[t][s] = (s < 4 * nblk) ? up[4 * s] : T(0);
         }
-        band_solve<T, NT, NBK>(uf, nblk, S.band);
+        band_solve<T, NT, NBLK>(uf, nblk, 0, S.band);
     }
     if constexpr (RG > 1) lds_barrier();   // the other row groups have read the band
     if (act && rg == 0) {
@@ -591,7 +592,7 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
             cok[t][e] = c < c1;
             coff[t][e] = min(c, c1 - 1) * ld;
         }
-    // staging: thread tid brings elements tid + TB e of a 16 RG x 64 tile
+    // staging: thread tid brings elements tid + TB e of a 16 RG x 16 NBLK tile
     // (rows fastest) into fragment order
     const int nit = (n - kend + 16 * RG - 1) / (16 * RG);
     const int sr = tid % (16 * RG), sk = tid / (16 * RG);
@@ -657,47 +658,44 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
     lds_barrier();   // the tiles are free again
 }
 
-// Largest number of 16-column tiles per wavefront and round: as many as the
-// registers hold next to the C tiles in flight.
-template <typename T> struct Ntm;
-template <> struct Ntm<double> { static constexpr int v = 3; };
-template <> struct Ntm<float> { static constexpr int v = 4; };
-
-template <typename T, int TB, int RG, int NT>
+template <typename T, int TB, int RG, int NT, int NBLK, typename Lds>
 __device__ __forceinline__ void blk_rounds(int nt, T *A, int ld, int n, int kb, int kend, int c0, int c1, int nblk,
-                                           BlkLds<T, TB> &S) {
+                                           Lds &S) {
     if constexpr (NT >= 1) {
         if (nt == NT) {
 #pragma unroll 1
             for (int cs = c0; cs < c1; cs += 16 * NT * (TB / 64 / RG))
-                blk_round<T, TB, NT, RG>(A, ld, n, kb, kend, cs, c1, nblk, S);
+                blk_round<T, TB, NT, RG, NBLK>(A, ld, n, kb, kend, cs, c1, nblk, S);
         } else {
-            blk_rounds<T, TB, RG, NT - 1>(nt, A, ld, n, kb, kend, c0, c1, nblk, S);
+            blk_rounds<T, TB, RG, NT - 1, NBLK>(nt, A, ld, n, kb, kend, c0, c1, nblk, S);
         }
     }
 }
 
 // Columns [c0, c1) right of the super-panel kb..kend.
-template <typename T, int TB>
-__device__ __forceinline__ void blk_update(T *A, int ld, int n, int kb, int kend, int c0, int c1, BlkLds<T, TB> &S) {
-    constexpr int W = TB / 64, NTM = Ntm<T>::v;
+// NTM: largest number of 16-column tiles per wavefront and round, as many as
+// the instance's registers hold next to the C tiles in flight.
+template <typename T, int TB, int NTM, int NBLK, typename Lds>
+__device__ __forceinline__ void blk_update(T *A, int ld, int n, int kb, int kend, int c0, int c1, Lds &S) {
+    constexpr int W = TB / 64;
     const int nblk = (kend - kb + NB - 1) / NB;
     const int ct = (c1 - c0 + 15) / 16, rt = (n - kend + 15) / 16;
     // fewest products on the longest wavefront, one row group or two: rounds
     // x tiles per wavefront x row tiles, with the band solve counted as the
-    // ten 16-row products it is
+    // 16-row products it is
+    constexpr int BS = NBLK * (NBLK + 1) / 2;
     const int r1 = (ct + W * NTM - 1) / (W * NTM), n1 = (ct + r1 * W - 1) / (r1 * W);
     const int r2 = (ct + W / 2 * NTM - 1) / (W / 2 * NTM), n2 = (ct + r2 * (W / 2) - 1) / (r2 * (W / 2));
-    if (r1 * n1 * (4 * rt + 10) <= r2 * n2 * (2 * (rt + 1) + 10))
-        blk_rounds<T, TB, 1, NTM>(n1, A, ld, n, kb, kend, c0, c1, nblk, S);
+    if (r1 * n1 * (NBLK * rt + BS) <= r2 * n2 * (NBLK / 2 * (rt + 1) + BS))
+        blk_rounds<T, TB, 1, NTM, NBLK>(n1, A, ld, n, kb, kend, c0, c1, nblk, S);
     else
-        blk_rounds<T, TB, 2, NTM>(n2, A, ld, n, kb, kend, c0, c1, nblk, S);
+        blk_rounds<T, TB, 2, NTM, NBLK>(n2, A, ld, n, kb, kend, c0, c1, nblk, S);
 }
 
 // The diagonal block of the back substitution: lane = row, up to NR
 // right-hand sides side by side in a wavefront.
-template <typename T, int TB, int NR>
-__device__ __forceinline__ void blk_diag(int n, int K, int rb, int w, double *X, BlkLds<T, TB> &S) {
+template <typename T, int TB, int NR, typename Lds>
+__device__ __forceinline__ void blk_diag(int n, int K, int rb, int w, double *X, Lds &S) {
     constexpr int W = TB / 64;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (wave >= K) return;
@@ -741,8 +739,8 @@ __device__ __forceinline__ void blk_diag(int n, int K, int rb, int w, double *X,
 // diagonal block in LDS, one right-hand side per wavefront at a time (lane =
 // row), then the rows above take the block's contribution on the matrix
 // cores, all right-hand sides at once (U is read once).
-template <typename T, int TB>
-__device__ __forceinline__ void blk_back(const T *A, int ld, int n, int K, double *X, BlkLds<T, TB> &S) {
+template <typename T, int TB, typename Lds>
+__device__ __forceinline__ void blk_back(const T *A, int ld, int n, int K, double *X, Lds &S) {
     constexpr int W = TB / 64;
     typedef typename TileMap<T>::acc acc_t;
     ld = opaque_s(ld);
@@ -820,8 +818,8 @@ __device__ __forceinline__ void blk_back(const T *A, int ld, int n, int K, doubl
 
 // Factor airfoil b's system in place and solve its K right-hand sides, one
 // workgroup of TB threads.
-template <typename T, int TB, int RMAX>
-__device__ __forceinline__ void blk_lu(const WsView &v, int b, int32_t *__restrict__ info_out, BlkLds<T, TB> &S) {
+template <typename T, int TB, int RMAX, int NTM, int H = 1, typename Lds>
+__device__ __forceinline__ void blk_lu(const WsView &v, int b, int32_t *__restrict__ info_out, Lds &S) {
     const AirfoilMeta mt = v.meta[b];
     const int n = mt.n1, ld = mt.ld, ncols = mt.n1 + mt.K;
     const int tid = threadIdx.x;
@@ -842,28 +840,39 @@ __device__ __forceinline__ void blk_lu(const WsView &v, int b, int32_t *__restri
     T *A = wv::sys_of<T>(v, mt);
     int32_t *piv = v.piv + mt.piv_off;
     int info = 0;
-    for (int K0 = 0; K0 < n; K0 += BSP) {
-        const int kend = min(K0 + BSP, n);
-        for (int k0 = K0; k0 < kend; k0 += NB) {
-            const int nb = min(NB, n - k0), i = (k0 - K0) / NB;
-            const int rows = (n - k0 + TB - 1) / TB;
-            if (rows == 1)
-                blk_panel<T, 1, TB>(A, ld, n, K0, k0, nb, piv, info, S);
-            else if (RMAX == 2 || rows == 2)
-                blk_panel<T, 2, TB>(A, ld, n, K0, k0, nb, piv, info, S);
-            else
-                blk_panel<T, RMAX, TB>(A, ld, n, K0, k0, nb, piv, info, S);
-            blk_moves<T, TB>(A, ld, ncols, k0, nb, S);
-            if (tid >= TB - 64) blk_linv<T, TB>(i, S);
-            __syncthreads();
-            // block row i of the band (its rows are final now)
-            for (int idx = tid; idx < 256 * i; idx += TB) {
-                const int r = idx & 15, k = idx >> 4;   // k: column within the band
-                S.band[pair_at(i, k >> 4)][frag_at<T>(r, k & 15)] = A[(size_t)(K0 + k) * ld + k0 + r];
+    // super-panels of H halves of 64 columns: with H = 2 the first half updates
+    // the second one only, and the columns to the right of both take one
+    // rank-128 update
+    for (int KS = 0; KS < n; KS += BSP * H) {
+        const int ks1 = min(KS + BSP * H, n);
+#pragma unroll 1
+        for (int K0 = KS; K0 < ks1; K0 += BSP) {
+            const int kend = min(K0 + BSP, n), i0 = (K0 - KS) / NB;
+            for (int k0 = K0; k0 < kend; k0 += NB) {
+                const int nb = min(NB, n - k0), i = (k0 - KS) / NB;
+                const int rows = (n - k0 + TB - 1) / TB;
+                if (rows == 1)
+                    blk_panel<T, 1, TB>(A, ld, n, K0, k0, nb, i0, piv, info, S);
+                else if (RMAX == 2 || rows == 2)
+                    blk_panel<T, 2, TB>(A, ld, n, K0, k0, nb, i0, piv, info, S);
+                else
+                    blk_panel<T, (RMAX > 2 ? RMAX : 2), TB>(A, ld, n, K0, k0, nb, i0, piv, info, S);
+                blk_moves<T, TB>(A, ld, ncols, k0, nb, S);
+                if (tid >= TB - 64) blk_linv<T, TB>(i, S);
+                __syncthreads();
+                // block row i of the band (its rows are final now)
+                for (int idx = tid; idx < 256 * i; idx += TB) {
+                    const int r = idx & 15, k = idx >> 4;   // k: column within the band
+                    S.band[pair_at(i, k >> 4)][frag_at<T>(r, k & 15)] = A[(size_t)(KS + k) * ld + k0 + r];
+                }
+                __syncthreads();
             }
-            __syncthreads();
+            if (H == 2 && i0 == 0 && kend < ks1) {
+                blk_update<T, TB, NTM, NBK>(A, ld, n, K0, kend, kend, ks1, S);
+                __syncthreads();
+            }
         }
-        blk_update<T, TB>(A, ld, n, K0, kend, kend, ncols, S);   // (the right-hand sides at least)
+        blk_update<T, TB, NTM, NBK * H>(A, ld, n, KS, ks1, ks1, ncols, S);   // (the right-hand sides at least)
         __syncthreads();
     }
     if (tid == 0) {
