@@ -142,7 +142,10 @@ panel_status panel_plan_set_formulation(panel_plan *plan, int32_t formulation);
  *                wg_waves = 8, always take separate launches.
  *   wg_waves     wavefronts per workgroup-factored system: 4, 8, or 0 (eight
  *                when the batch has at most one airfoil per CU; systems above
- *                768 rows always take eight)
+ *                768 rows always take eight).  With 0, and persistent = 0,
+ *                small batches also factor the systems within wave_max_n1 by
+ *                a workgroup each, and refine them so where they have several
+ *                angles
  * Default {320, 0, 0} (the faster choice on the batches measured; the
  * persistent kernel holds both paths and spills more registers).  Changing
  * wave_max_n1 takes effect at the next panel_workspace_init, as for

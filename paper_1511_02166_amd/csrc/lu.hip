@@ -29,12 +29,11 @@ namespace {
 
 constexpr int TPB = 256;   // threads per workgroup by default (4 wavefronts)
 
-// Eight wavefronts per airfoil for the workgroup kernels: by default when
-// the batch has at most one airfoil per CU (measured: 256 sections at
-// N = 1024, 24.4 -> 19.9 ms in FP64; with more airfoils than CUs, four per
-// airfoil and two airfoils per CU keep more systems in flight: 4096
-// airfoils, N = 96..512, 17.2 ms against 22.6), and always for systems of
-// more than 768 rows.
+// Eight wavefronts per airfoil for the workgroup kernels: by default when the
+// batch has at most one airfoil per CU (256 systems of order 257: 441 -> 430 us
+// in FP64; with more airfoils than CUs, four per airfoil and two airfoils per
+// CU keep more systems in flight: 512 of order 257 608 us against 877), and
+// always for systems of more than 768 rows.
 bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
     if (max_n1 > 3 * TPB) return true;
     if (wg_waves == 4) return false;

@@ -97,7 +97,7 @@ hipError_t launch_assemble(const WsView &v, int32_t B, int32_t max_cols, int32_t
                            const double *xy, const double *alpha, const double *chord, double vinf,
                            hipStream_t stream);
 // Systems of order up to PANEL_WAVE_MAX_N1 can be factored by one wavefront
-// each (lu_wave.hip); larger ones by a workgroup each (lu.hip).  The plan
+// each (lu_wave.hip); larger ones by a workgroup each (lu_block.hip).  The plan
 // puts the workgroup-kernel airfoils first in `order` (n_block of them, each
 // group in LPT order).
 constexpr int PANEL_WAVE_RMAX = 5;
@@ -106,7 +106,9 @@ constexpr int PANEL_WAVE_MAX_N1 = 64 * PANEL_WAVE_RMAX;
 // (and refines each FP32 solution right after its factorisation); used when
 // every workgroup-kernel system fits four wavefronts (n1 <= 768) and
 // wg_waves != 8.  wg_waves: 4 or 8 wavefronts per workgroup-kernel system,
-// 0 = eight when the batch has at most one airfoil per CU.
+// 0 = eight when the batch has at most one airfoil per CU.  max_n1_small: the
+// largest order among the others; small_eff: their number, each weighted by
+// (order / max_n1_small)^2; max_k: the most right-hand sides of an airfoil.
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
                                int32_t max_n1_small, double small_eff, int32_t max_k, int32_t mixed, double tol,
                                int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream);
@@ -115,8 +117,8 @@ hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t
 // (airfoils with more than kmax right-hand sides are left to another kernel)
 hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t kmax, int32_t *info, double tol,
                               int32_t max_iter, hipStream_t stream);
-// Systems at the front of the order, a workgroup of `waves` (4 or 8)
-// wavefronts each (lu_block.hip).
+// Systems at the front of the order (orders up to max_n1; with four wavefronts
+// at most 768), a workgroup of `waves` (4 or 8) wavefronts each (lu_block.hip).
 hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_t max_n1, int32_t mixed, int32_t *info,
                            hipStream_t stream);
 // `count` airfoils of the order from `first` on (orders up to max_n1; with four

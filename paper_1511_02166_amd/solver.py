@@ -111,7 +111,8 @@ class PanelSolver:
             big = n1 > wl
             nb = int(big.sum())
             key_part = tuple(np.flatnonzero(big)) if 0 < nb < len(n1) else nb
-            wgs = (0,) if nb == 0 else ((8,) if int(n1.max()) > 768 else (4, 8))
+            # 0 leaves the workgroups, and whether small systems get one each, to the library
+            wgs = (0,) if nb == 0 else ((0, 8) if int(n1.max()) > 768 else (0, 4, 8))
             for pers in (1, 0):
                 for wg in wgs:
                     # one launch applies only where the workgroup systems fit four wavefronts
