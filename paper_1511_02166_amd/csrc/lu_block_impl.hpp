@@ -1,6 +1,7 @@
 // lu_block_impl.hpp -- one workgroup factors one system: batched LU with
 // partial pivoting and the back substitution, for systems of up to
-// RMAX * TB rows.  Device functions only; lu.hip holds the kernels.
+// RMAX * TB rows.  Device functions only; the kernels are in lu_block.hip and
+// lu_batch.hip.
 //
 // Sec. 3 of the paper: every airfoil needs the LU decomposition of its dense
 // system.  One wavefront per system (lu_wave_impl.hpp) keeps the GPU full
