@@ -533,6 +533,11 @@ __device__ __forceinline__ void blk_linv(int i, Lds &S) {
     }
 }
 
+// TileMap::col as lane * (lane group) + step * element.
+template <typename T> struct ColMap;
+template <> struct ColMap<double> { static constexpr int lane = 1, step = 4; };
+template <> struct ColMap<float> { static constexpr int lane = 4, step = 1; };
+
 // ---- trailing update ---------------------------------------------------------
 // One round: 16 NT columns per column group of wavefronts, starting at cs0
 // (columns up to c1); RG row groups of wavefronts share each column group.
@@ -583,16 +588,35 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
             uf[t][s] = -uf[t][s];
             asm volatile("" : "+v"(uf[t][s]));
         }
-    int coff[NT][4];
-    bool cok[NT][4];
+    // C columns of this lane, col(lane, e) = lane part + uniform part.  In FP32
+    // and in the rank-128 rounds, a round of whole columns reads each (t, e) at
+    // a scalar base plus one per-lane offset, which saves two or three vector
+    // instructions per access (whole FP32 step of 256 sections of order 1025:
+    // 7.08 -> 6.94 ms, of the uneven batch of 4096 9.50 -> 9.42 ms);
+    // the other FP64 rounds, and those that run past c1, keep an element
+    // offset per column (one system of order 161: 227 us against 231).
+    constexpr bool SB = sizeof(T) == 4 || NBLK > NBK;
+    constexpr int LC = ColMap<T>::lane, UC = ColMap<T>::step;
+    const bool whole = SB && cs + 16 * NT <= c1;   // wave-uniform
+    const char *cbase = reinterpret_cast<const char *>(A + (size_t)min(cs, c1 - 1) * ld);
+    const unsigned clane = (unsigned)(LC * k4 * ld) * (unsigned)sizeof(T);
+    auto cptr = [&](int t, int e, int r) {
+        return reinterpret_cast<T *>(const_cast<char *>(cbase) + (size_t)((16 * t + UC * e) * ld) * sizeof(T) +
+                                     (clane + (unsigned)r * (unsigned)sizeof(T)));
+    };
+    int coff[SB ? 1 : NT][4];
+    bool cok[SB ? 1 : NT][4];
+    if constexpr (!SB) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = cs + 16 * t + TileMap<T>::col(lane, e);
-            cok[t][e] = c < c1;
-            coff[t][e] = min(c, c1 - 1) * ld;
-        }
+            for (int e = 0; e < 4; ++e) {
+                const int c = cs + 16 * t + LC * k4 + UC * e;
+                cok[t][e] = c < c1;
+                coff[t][e] = min(c, c1 - 1) * ld;
+            }
+    }
+    auto ccol = [&](int t, int e) { return cs + 16 * t + LC * k4 + UC * e; };
     // staging: thread tid brings elements tid + TB e of a 16 RG x 16 NBLK tile
     // (rows fastest) into fragment order
     const int nit = (n - kend + 16 * RG - 1) / (16 * RG);
@@ -616,10 +640,22 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
     T cb[NT][4];
     auto load_c = [&](int it) {
         const int r = min(kend + 16 * (RG * it + rg) + i16, n - 1);
+        if (whole) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) cb[t][e] = A[coff[t][e] + r];
+                for (int e = 0; e < 4; ++e) cb[t][e] = *cptr(t, e, r);
+        } else {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (SB)
+                        cb[t][e] = A[(size_t)min(ccol(t, e), c1 - 1) * ld + r];
+                    else
+                        cb[t][e] = A[coff[t][e] + r];
+                }
+        }
     };
     load_l(0);
     store_l(0);
@@ -647,11 +683,22 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
             }
             const int r = kend + 16 * (RG * it + rg) + i16;
             if (r < n) {
+                if (whole) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+                    for (int t = 0; t < NT; ++t)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (cok[t][e]) A[coff[t][e] + r] = cb[t][e] + acc[t][e];
+                        for (int e = 0; e < 4; ++e) *cptr(t, e, r) = cb[t][e] + acc[t][e];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if constexpr (SB) {
+                                if (ccol(t, e) < c1) A[(size_t)ccol(t, e) * ld + r] = cb[t][e] + acc[t][e];
+                            } else {
+                                if (cok[t][e]) A[coff[t][e] + r] = cb[t][e] + acc[t][e];
+                            }
+                }
             }
             load_c(it + 1);
         }
