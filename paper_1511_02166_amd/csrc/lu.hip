@@ -69,10 +69,10 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
     const int32_t waves = eight_waves(n_block, max_n1_block, wg_waves) ? 8 : 4;
     if (wg_waves == 0 && small_in_blocks(max_n1_small, small_eff, mixed)) {
         // every system by a workgroup, in one launch
-        e = launch_lu_block(v, B, n_block > 0 && eight_waves(B, max_n1_block, 0) ? 8 : 4,
+        e = launch_lu_block(v, B, n_block, n_block > 0 && eight_waves(B, max_n1_block, 0) ? 8 : 4,
                             n_block > 0 ? max_n1_block : max_n1_small, mixed, info, stream);
     } else {
-        e = launch_lu_block(v, n_block, waves, max_n1_block, mixed, info, stream);
+        e = launch_lu_block(v, n_block, n_block, waves, max_n1_block, mixed, info, stream);
         if (e == hipSuccess) e = launch_lu_wave(v, n_block, B - n_block, mixed, info, stream);
     }
     if (e != hipSuccess) return e;

@@ -34,7 +34,7 @@ template <typename T> union BatchLds {
 template <typename T>
 __device__ __forceinline__ void batch_wg_item(const WsView &v, int b, int32_t *info, int mixed, double tol,
                                            int max_iter, BatchLds<T> &S) {
-    blk::blk_lu<T, TPB, 3, sizeof(T) == 8 ? 3 : 4>(v, b, info, S.lu);
+    blk::blk_lu<T, TPB, 3, sizeof(T) == 8 ? 3 : 4>(v, b, 3 * TPB, info, S.lu);
     __syncthreads();
     if (mixed) {
         rfb::wg_refine<TPB, 4, 768>(v, b, info, tol, max_iter, S.ref);

@@ -865,17 +865,18 @@ __device__ __forceinline__ void blk_back(const T *A, int ld, int n, int K, doubl
 }
 
 // Factor airfoil b's system in place and solve its K right-hand sides, one
-// workgroup of TB threads.
+// workgroup of TB threads; systems of more than max_n (at most RMAX * TB) rows
+// are refused.
 template <typename T, int TB, int RMAX, int NTM, int H = 1, typename Lds>
-__device__ __forceinline__ void blk_lu(const WsView &v, int b, int32_t *__restrict__ info_out, Lds &S) {
+__device__ __forceinline__ void blk_lu(const WsView &v, int b, int max_n, int32_t *__restrict__ info_out, Lds &S) {
     const AirfoilMeta mt = v.meta[b];
     const int n = mt.n1, ld = mt.ld, ncols = mt.n1 + mt.K;
     const int tid = threadIdx.x;
     double *X = v.x + mt.x_off;
-    if (v.flag[b] != 0 || n > RMAX * TB) {
-        // screened out by the assembly (-1), or a system too large for this
-        // kernel (-3: the workspace's airfoil order does not match the plan
-        // it is used with)
+    if (v.flag[b] != 0 || n > max_n) {
+        // screened out by the assembly (-1), or a system too large for its
+        // place in the order (-3: the workspace's airfoil order does not match
+        // the plan it is used with)
         const int code = v.flag[b] != 0 ? -1 : -3;
         __syncthreads();
         if (tid == 0) {

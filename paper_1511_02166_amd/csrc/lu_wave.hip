@@ -18,7 +18,23 @@ __global__ __launch_bounds__(WL, 2) void refine_wave_kernel(WsView v, int32_t fi
                                                          int32_t *__restrict__ info, double tol, int max_iter) {
     __shared__ WaveRefLds W;
     const int b = v.order[first + blockIdx.x];
-    if (v.meta[b].K > kmax) return;
+    const AirfoilMeta mt = v.meta[b];
+    if (mt.K > kmax) return;
+    if (mt.n1 > WL * PANEL_WAVE_RMAX) {
+        // too large for one wavefront: the workspace's airfoil order does not
+        // match the plan.  The factorisation has refused such a system already;
+        // its LDS vectors here end at this order, so nothing rests on that.
+        if (info[b] == 0) {
+            double *X = v.x + mt.x_off;
+            for (int i = wlane(); i < mt.n1 * mt.K; i += WL) X[i] = __builtin_nan("");
+            if (wlane() == 0) info[b] = -3;
+        }
+        if (wlane() == 0) {
+            v.iters[b] = 0;
+            v.flag[b] = info[b];
+        }
+        return;
+    }
     wave_refine(v, b, info, tol, max_iter, W);
 }
 

@@ -118,9 +118,10 @@ hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t
 hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t kmax, int32_t *info, double tol,
                               int32_t max_iter, hipStream_t stream);
 // Systems at the front of the order (orders up to max_n1; with four wavefronts
-// at most 768), a workgroup of `waves` (4 or 8) wavefronts each (lu_block.hip).
-hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t waves, int32_t max_n1, int32_t mixed, int32_t *info,
-                           hipStream_t stream);
+// at most 768; those from n_block on within the wave limit), a workgroup of
+// `waves` (4 or 8) wavefronts each (lu_block.hip).
+hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t n_block, int32_t waves, int32_t max_n1,
+                           int32_t mixed, int32_t *info, hipStream_t stream);
 // `count` airfoils of the order from `first` on (orders up to max_n1; with four
 // wavefronts at most 768), those with at least kmin right-hand sides
 // (refine_block.hip).

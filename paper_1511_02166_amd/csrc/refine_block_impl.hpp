@@ -367,16 +367,24 @@ __device__ __forceinline__ void wg_refine(const WsView &v, int b, int32_t *__res
     const AirfoilMeta mt = v.meta[b];
     const int n = mt.n1, ld = mt.ld;
     const int tid = threadIdx.x;
-    if (info[b] != 0 || n > NM) {   // (n > NM: the caller's choice of instance excludes it)
+    double *X = v.x + mt.x_off;
+    const int before = info[b];   // (read by all before it is written below)
+    if (before != 0 || n > NM) {
+        // not factored, or a system too large for this instance (-3: the
+        // workspace's airfoil order does not match the plan)
+        const int code = before != 0 ? before : -3;
+        if (before == 0)
+            for (int i = tid; i < n * mt.K; i += TB) X[i] = __builtin_nan("");
+        __syncthreads();
         if (tid == 0) {
             v.iters[b] = 0;
-            v.flag[b] = info[b];
+            info[b] = code;
+            v.flag[b] = code;
         }
         return;
     }
     const double *A = v.a64 + mt.a_off;
     const float *LU = v.a32 + mt.a_off;
-    double *X = v.x + mt.x_off;
     perm_of_pivots(v.piv + mt.piv_off, n, TB, S.perm);
     for (int i = tid; i < n; i += TB) S.pinv[S.perm[i]] = (unsigned short)i;
     const double floor_c = sqrt((double)n) * 2.220446049250313e-16;
