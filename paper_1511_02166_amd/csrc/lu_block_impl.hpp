@@ -90,19 +90,30 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v) {
     return max(max(a, b), max(c, d));
 }
 
-// 1 / x to about an ulp (x uniform over the wavefront): the hardware estimate
-// and two Newton steps; a division costs several times their latency, once
-// per pivot column.  Outside the range where the steps cannot overflow, the
-// division itself.
-__device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    r = fma(fma(-x, r, 1.0), r, r);
-    const unsigned h = (unsigned)__builtin_amdgcn_readfirstlane(__double2hiint(x)) & 0x7fffffffu;
-    if (h < 0x04000000u || h > 0x7bf00000u) r = 1.0 / x;   // |x| below 2^-959 or above 2^960
-    return r;
+// The multipliers a / x of one column step, x the pivot (uniform over the
+// workgroup, |a| <= |x|) and kmax its prefix.  FP64: with r the hardware
+// estimate (2^-23) after one Newton step, a r corrected by its own remainder,
+// which leaves the rounding of the last step (0.5 ulp; a r alone is off by up to
+// 1.5); a division costs several times the latency, once per pivot column.
+// Where r or a remainder could leave the normal range, the division itself.
+template <int R> __device__ __forceinline__ void multipliers(double (&l)[R], double x, unsigned kmax) {
+    if (__builtin_expect(kmax > 0x04000000u && kmax <= 0x7bf00000u, 1)) {   // 2^-959 <= |x| < 2^960
+        double r = __builtin_amdgcn_rcp(x);
+        r = fma(fma(-x, r, 1.0), r, r);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const double t = l[q] * r;
+            l[q] = fma(fma(-x, t, l[q]), r, t);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < R; ++q) l[q] = l[q] / x;
+    }
 }
-__device__ __forceinline__ float recip(float x) { return 1.0f / x; }
+template <int R> __device__ __forceinline__ void multipliers(float (&l)[R], float x, unsigned) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) l[q] = l[q] / x;
+}
 
 // Position of element (row r, column k) of a 16x16 block in the A-operand
 // fragment order of the band solve: [lane][k-step].
@@ -228,7 +239,10 @@ __device__ __forceinline__ void blk_col(T (&p)[R][NB], int (&pos)[R], unsigned &
         for (int e = 0; e < VW; ++e) u[VW * c + e] = x[e];
     }
     const int ppos = S.cpos[buf][pw];
-    const T rinv = recip(u[C]);
+    T l[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) l[q] = p[q][C];
+    multipliers<R>(l, u[C], kmax);
     // the pivot row moves to position g (and leaves the candidates), the row
     // at g to the pivot row's position
 #pragma unroll
@@ -244,8 +258,8 @@ __device__ __forceinline__ void blk_col(T (&p)[R][NB], int (&pos)[R], unsigned &
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         const bool lv = (live >> q) & 1u;
-        const T l = p[q][C] * rinv, lm = lv ? l : T(0);
-        p[q][C] = lv ? l : p[q][C];
+        const T lm = lv ? l[q] : T(0);
+        p[q][C] = lv ? l[q] : p[q][C];
 #pragma unroll
         for (int cc = C + 1; cc < NB; ++cc) p[q][cc] -= lm * u[cc];
     }
