@@ -111,12 +111,16 @@ class PanelSolver:
             big = n1 > wl
             nb = int(big.sum())
             key_part = tuple(np.flatnonzero(big)) if 0 < nb < len(n1) else nb
-            # 0 leaves the workgroups, and whether small systems get one each, to the library
-            wgs = (0,) if nb == 0 else ((0, 8) if int(n1.max()) > 768 else (0, 4, 8))
+            # 0 leaves the workgroups, and whether small systems get one each, to the library;
+            # 4 and 8 keep the small systems on the one-wavefront kernels
+            wgs = (0, 4) if nb == 0 else ((0, 8) if int(n1.max()) > 768 else (0, 4, 8))
             for pers in (1, 0):
                 for wg in wgs:
-                    # one launch applies only where the workgroup systems fit four wavefronts
+                    # one launch applies only where the workgroup systems fit four wavefronts,
+                    # and is the same for every wg without any
                     eff_pers = pers if (nb == 0 or wg == 4) else 0
+                    if nb == 0 and eff_pers and wg:
+                        continue
                     key = (key_part, eff_pers, wg)
                     if key in seen:
                         continue
