@@ -294,7 +294,8 @@ hipError_t launch_adjoint(const WsView &v, int32_t B, int32_t n_block, int32_t m
             // but 1024 0.29 against 0.27 and 1024 of order 257 0.81 against
             // 0.61; FP32 factors 1.54 against 1.30 at order 129, 0.53 against
             // 0.58 at 65
-            if (B - n_block > 6 * device_cus() && max_n1_small <= (mixed ? 80 : 144)) {
+            if (B - n_block > 6 * device_cus() &&
+                max_n1_small <= (mixed ? ADJOINT_WAVE_MAX_F32 : ADJOINT_WAVE_MAX_F64)) {
                 const hipError_t e =
                     launch_adjoint_wave(v, n_block, B - n_block, mixed, xy, dcl, dcp, ka, dxy, info, stream);
                 if (e != hipSuccess) return e;

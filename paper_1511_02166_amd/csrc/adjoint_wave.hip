@@ -1,5 +1,6 @@
 // adjoint_wave.hip -- reverse-mode lift sensitivity, one wavefront per
-// airfoil, for systems of up to 64 * PANEL_WAVE_RMAX rows.
+// airfoil, for systems of up to ADJOINT_WAVE_MAX_F64 rows (FP32 factors:
+// ADJOINT_WAVE_MAX_F32), the largest that launch_adjoint sends here.
 //
 // Same mathematics as adjoint.hip (the shape gradient of the Kutta-Joukowski
 // lift of the Sec. 2 panel system):
@@ -32,8 +33,13 @@ namespace panel {
 namespace {
 
 constexpr int WL = 64;
-constexpr int RM = PANEL_WAVE_RMAX;
-constexpr int NW = WL * RM;   // largest system order handled here
+// Control points per lane, as many as the largest order needs: the register
+// arrays and LDS vectors below are sized by it (five slots, for systems that never
+// came here: 4096 sections of order 65 with FP32 factors 522 us, now 504; of
+// order 97 in FP64 518, now 514).
+template <typename T> struct Slots {
+    static constexpr int v = ((sizeof(T) == 8 ? ADJOINT_WAVE_MAX_F64 : ADJOINT_WAVE_MAX_F32) + WL - 1) / WL;
+};
 constexpr double kInv2Pi = 0.15915494309189535;
 constexpr double kInv4Pi = 0.07957747154594767;
 
@@ -124,13 +130,17 @@ __device__ __forceinline__ void wave_solve_t(const T *LU, int ld, int n, const i
     __syncthreads();
 }
 
+// Two wavefronts per SIMD, also where the registers would hold three or four:
+// with those, eight sections per CU spread unevenly over the SIMDs (2048 of order
+// 113 in FP64 389 us against 324) and sections of mixed sizes evict each other's
+// factors (4096 of order 25 to 97, FP32: 525 against 459).  (More would win for
+// equal sections from about ten per CU on: 4096 of order 113 571 against 605.)
 template <typename T>
-__global__ __launch_bounds__(WL, 2) void adjoint_wave_kernel(WsView v, int32_t first,
-                                                             const double *__restrict__ xy,
-                                                             const double *__restrict__ dcl,
-                                                             const double *__restrict__ dcp, int32_t ka,
-                                                             double *__restrict__ dxy,
-                                                             int32_t *__restrict__ info) {
+__global__ __launch_bounds__(WL) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void adjoint_wave_kernel(WsView v, int32_t first, const double *__restrict__ xy, const double *__restrict__ dcl,
+                         const double *__restrict__ dcp, int32_t ka, double *__restrict__ dxy,
+                         int32_t *__restrict__ info) {
+    constexpr int RM = Slots<T>::v, NW = WL * RM;   // NW: largest order handled here
     const int b = v.order[first + blockIdx.x];
     const AirfoilMeta mt = v.meta[b];
     const int N = mt.N, n1 = mt.n1, K = mt.K, ld = mt.ld;

@@ -148,6 +148,9 @@ hipError_t launch_math_eval(int32_t n, const double *x, const double *y, double 
 hipError_t launch_adjoint(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block, int32_t max_n1_small,
                           int32_t max_k, int32_t mixed, const double *xy, const double *dcl, const double *dcp, double *dxy,
                           int32_t *info, hipStream_t stream);
+// Orders the one-wavefront adjoint is used for (the choice, and the reason for
+// these limits, in launch_adjoint).
+constexpr int ADJOINT_WAVE_MAX_F64 = 144, ADJOINT_WAVE_MAX_F32 = 80;
 hipError_t launch_adjoint_wave(const WsView &v, int32_t first, int32_t count, int32_t mixed, const double *xy,
                                const double *dcl, const double *dcp, int32_t ka, double *dxy, int32_t *info,
                                hipStream_t stream);
