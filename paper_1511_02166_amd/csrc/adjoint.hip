@@ -290,11 +290,16 @@ hipError_t launch_adjoint(const WsView &v, int32_t B, int32_t n_block, int32_t m
         if (B > n_block) {
             // a wavefront each (adjoint_wave.hip) only where short sections
             // leave a workgroup little to share and there are enough of them
-            // to fill the GPU: 4096 of order 129 0.81 ms against 0.92 (FP64),
-            // but 1024 0.29 against 0.27 and 1024 of order 257 0.81 against
-            // 0.61; FP32 factors 1.54 against 1.30 at order 129, 0.53 against
-            // 0.58 at 65
-            if (B - n_block > 6 * device_cus() &&
+            // to fill the GPU.  Wavefronts / workgroups, us, cl cotangents, by
+            // sections per CU: FP64, order 65: 138 / 130 at five, 149 / 185 at
+            // seven; order 144: 468 / 425 at six, 503 / 491 at seven, 535 / 550
+            // at eight.  FP32 factors, order 80: 338 / 330 at six, 388 / 400 at
+            // eight; order 97: 913 / 888 at sixteen.  The refinement of lambda
+            // leaves workgroups on the shortest systems idle sooner: FP32, order
+            // 25: 62 / 62 at four, 75 / 91 at five; order 49: 112 / 96 at four,
+            // 138 / 148 at five; order 65: 221 / 223 at five.
+            const int32_t per_cu = mixed && max_n1_small <= 56 ? 4 : 6;
+            if (B - n_block > per_cu * device_cus() &&
                 max_n1_small <= (mixed ? ADJOINT_WAVE_MAX_F32 : ADJOINT_WAVE_MAX_F64)) {
                 const hipError_t e =
                     launch_adjoint_wave(v, n_block, B - n_block, mixed, xy, dcl, dcp, ka, dxy, info, stream);

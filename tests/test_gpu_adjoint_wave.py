@@ -79,3 +79,22 @@ def test_bad_geometry_stays_with_its_section(precision):
     bad[2 * noff[7]:2 * noff[8]] = True
     assert np.all(np.isnan(g[bad])) and np.all(np.isfinite(g[~bad]))
     assert s.adj_info.cpu().numpy()[7] == -1 and np.sum(s.adj_info.cpu().numpy() != 0) == 1
+
+
+@pytest.mark.parametrize("n", [24, 48])
+def test_shortest_sections_with_fp32_factors_from_five_per_cu_on(n):
+    # the same sections alone (five per CU) and in a batch that is large enough
+    # for any order: the same kernel, so the same bits
+    import torch
+
+    import paper_1511_02166_amd as P
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sections = [_section(q, n) for q in range(6 * cus + 1)]
+    grads = []
+    for B in (5 * cus, 6 * cus + 1):
+        xy_flat, noff = synth.pack_nodes(sections[:B])
+        s = P.PanelSolver(noff, np.arange(B + 1, dtype=np.int32), P.PANEL_FP32_REFINE, tiling=(320, 0, 4))
+        xy = torch.as_tensor(xy_flat, device="cuda")
+        s.step(xy, torch.full((B,), 0.05, dtype=torch.float64, device="cuda"))
+        grads.append(s.adjoint(xy, torch.ones(B, dtype=torch.float64, device="cuda")))
+    assert torch.equal(grads[0], grads[1][:grads[0].numel()])
