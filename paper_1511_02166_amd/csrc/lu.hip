@@ -30,10 +30,11 @@ namespace {
 constexpr int TPB = 256;   // threads per workgroup by default (4 wavefronts)
 
 // Eight wavefronts per airfoil for the workgroup kernels: by default when the
-// batch has at most one airfoil per CU (256 systems of order 257: 441 -> 430 us
-// in FP64; with more airfoils than CUs, four per airfoil and two airfoils per
-// CU keep more systems in flight: 512 of order 257 608 us against 877), and
-// always for systems of more than 768 rows.
+// batch has at most one airfoil per CU (four / eight wavefronts, 256 systems in
+// FP64: order 320 595 / 571 us; at 257 424 / 426 it no longer matters; with more
+// airfoils than CUs, four per airfoil and two airfoils per CU keep more systems
+// in flight: 512 of order 320 911 / 1159, of 257 622 / 868), and always for
+// systems of more than 768 rows.  (Small systems alone in a batch take four.)
 bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
     if (max_n1 > 3 * TPB) return true;
     if (wg_waves == 4) return false;
@@ -41,18 +42,40 @@ bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
     return n_block <= device_cus();
 }
 
-// Systems within the wave limit by a workgroup each instead of a wavefront
-// each.  A wavefront alone on its SIMD takes as long for one system as for a
-// thousand, so below about one and a half systems of the largest order per CU
-// (FP64; three in FP32, whose matrix cores are faster) the workgroups win.
-// Factor + solve, wavefronts against workgroups: FP64, one system of order
-// 161 (nine angles) 417 -> 236 us, 256 of order 129 204 -> 187 us, of 257
-// 653 -> 441 us, 680 of 66 to 320 next to 320 larger ones 3.13 -> 1.97 ms,
-// but 512 of order 129 220 -> 237 us and 256 of order 65 84 -> 91 us; with
-// FP32 refinement, 512 of order 129 321 -> 289 us, 1024 436 -> 550 us.
-bool small_in_blocks(int32_t max_n1_small, double small_eff, int32_t mixed) {
-    if (max_n1_small <= (mixed ? 64 : 96)) return false;
-    return small_eff <= (mixed ? 3.0 : 1.5) * device_cus();
+// Systems within the wave limit by a workgroup of four wavefronts each instead
+// of a wavefront each.  A wavefront alone on its SIMD takes as long for one
+// system as for a thousand; two workgroups share a CU.  Factor + solve,
+// wavefronts / workgroups, us, n_small systems of one order (FP32: the LU alone
+// differs, refinement by wavefronts on both sides):
+//   FP64     1/CU     1.5/CU   2/CU     2.5/CU   FP32   1/CU     2/CU     2.5/CU
+//   n1 = 97  136/119  141/143  143/148  170/243         177/158  187/173  205/259
+//   n1 = 105 139/125  146/149  147/152  176/256         187/170  196/184  218/281
+//   n1 = 113 168/141  173/169  178/174  213/288         210/182  218/198  243/301
+//   n1 = 129 205/170  212/205  217/211  259/349         262/225  273/245  305/369
+//   n1 = 161 282/212  296/261  303/270  316/445         337/271  359/304  411/457
+//   n1 = 257 647/424  695/561  725/622  774/991         704/508  859/705  919/1012
+//   n1 = 320 953/595  1023/865 1064/911 1163/1446       1024/741 1151/954 1229/1360
+// so equal systems stop at what is resident at once.  (At 65 in FP32: 114/110,
+// 126/125, 138/187.)  More of them pay only where the orders spread (`spread`:
+// their number over the number weighted by (order / largest)^2, small_eff), so
+// that short systems fill the gaps behind the long ones, and until the weighted
+// number per CU (before the colon) reaches a limit that grows with the order:
+//   FP64, 24-104: 1.03: 143/133, 1.35: 143/159;  65-104: 1.48: 146/189;  24-128:
+//   1.28: 212/187, 1.61: 216/224;  24-200: 1.50: 406/360, 1.79: 419/444;
+//   150-256: 2.01: 770/694, 2.52: 794/791;  200-319: 1.48: 1051/808, 2.64:
+//   1255/1196;  24-319: 2.16: 1147/1051, 2.92: 1290/1396;  but 200-256 (spread
+//   1.25): 1.75: 752/762, and 260-319 (1.21): 1.81: 1180/1199
+//   FP32, 24-104: 1.70: 195/210;  24-128: 1.61: 273/263, 1.93: 279/310;  128-200:
+//   1.61: 489/467, 2.14: 554/565;  150-256: 2.52: 920/866;  200-256: 1.75:
+//   857/785, 2.49: 937/919;  200-319: 2.64: 1316/1230;  24-319: 2.16: 1243/1132, 2.92: 1401/1415
+bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t mixed) {
+    const int32_t n = max_n1_small, cus = device_cus();
+    if (n <= (mixed ? 64 : 96)) return false;
+    const double per_cu = small_eff / cus, spread = n_small / small_eff;
+    if (n_small <= 2 * cus) return mixed || n > 112 || per_cu <= 1.6;
+    if (!mixed) return spread >= 1.4 && per_cu <= (n <= 112 ? 1.2 : n <= 224 ? 1.5 : 2.25);
+    if (n <= 144) return spread >= 1.5 && per_cu <= 1.65;
+    return n <= 224 ? spread >= 1.4 && per_cu <= 2.0 : spread >= 1.2 && per_cu <= 2.65;
 }
 
 }  // namespace
@@ -67,7 +90,7 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
         return launch_lu_batch(v, grid, B, n_block, mixed, tol, max_iter, info, stream);
     }
     const int32_t waves = eight_waves(n_block, max_n1_block, wg_waves) ? 8 : 4;
-    if (wg_waves == 0 && small_in_blocks(max_n1_small, small_eff, mixed)) {
+    if (wg_waves == 0 && small_in_blocks(B - n_block, max_n1_small, small_eff, mixed)) {
         // every system by a workgroup, in one launch
         e = launch_lu_block(v, B, n_block, n_block > 0 && eight_waves(B, max_n1_block, 0) ? 8 : 4,
                             n_block > 0 ? max_n1_block : max_n1_small, mixed, info, stream);
