@@ -78,6 +78,27 @@ bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, in
     return n <= 224 ? spread >= 1.4 && per_cu <= 2.0 : spread >= 1.2 && per_cu <= 2.65;
 }
 
+// Refinement of the systems within the wave limit: a workgroup each where it
+// reads the matrix once for several right-hand sides, or where the batch leaves
+// most SIMDs idle.  Wavefronts / workgroups, us (with the same LU before them),
+// systems of one order:
+//   one angle, order 33, 129, 257: 1/CU 60/60, 261/237, 706/647;  2/CU 63/66,
+//   276/270, 861/802;  2.5/CU 69/90, 308/354, 921/964
+//   two angles, order 33, 65, 89, 97: 4/CU 101/104, 205/203, 262/239, 297/273;
+//   6/CU 116/134, 233/259, 299/304, 342/342;  16/CU 229/314, 512/628, 740/751,
+//   898/839
+//   three angles, order 25, 33, 49: 8/CU 133/130, 167/167, 225/209;  16/CU
+//   236/252, 297/318, 407/398;  four angles, order 25: 16/CU 291/256; order 201:
+//   8/CU 2330/1349
+// A wavefront each where the tiling fixes the workgroups.
+RefineSplit refine_split(int32_t n_small, int32_t max_n1_small, int32_t wg_waves) {
+    const int32_t cus = device_cus();
+    if (wg_waves != 0) return {PANEL_KMAX + 1, 0, 0};
+    if (n_small <= 2 * cus && max_n1_small > 64) return {1, 0, 0};
+    if (n_small <= 4 * cus) return {2, 0, 0};
+    return {2, 88, 40};
+}
+
 }  // namespace
 
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
@@ -100,22 +121,17 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
     }
     if (e != hipSuccess) return e;
     if (mixed) {
-        e = launch_refine_block(v, 0, n_block, 1, max_n1_block, max_k, waves, info, tol, max_iter, stream);
+        const RefineSplit all{1, 0, 0};
+        e = launch_refine_block(v, 0, n_block, all, max_n1_block, max_k, waves, info, tol, max_iter, stream);
         if (e != hipSuccess) return e;
-        // Small systems: a workgroup each where it reads the matrix for
-        // several right-hand sides (2048 systems of order 201, four angles:
-        // 1.96 -> 0.99 ms) or where the batch leaves most SIMDs idle (256 of
-        // order 129: 84 -> 60 us, 512: 46 -> 41, but 1024: 106 -> 170); a
-        // wavefront each otherwise, and where the tiling fixes the
-        // workgroups.
         const int32_t n_small = B - n_block;
-        const int32_t kw = wg_waves != 0 ? PANEL_KMAX : n_small <= 2 * device_cus() ? 0 : 1;
-        if (max_k > kw) {
-            e = launch_refine_block(v, n_block, n_small, kw + 1, PANEL_WAVE_MAX_N1, max_k, 4, info, tol,
-                                    max_iter, stream);
+        const RefineSplit split = refine_split(n_small, max_n1_small, wg_waves);
+        if (refine_in_block(split, max_k, max_n1_small)) {
+            e = launch_refine_block(v, n_block, n_small, split, PANEL_WAVE_MAX_N1, max_k, 4, info, tol, max_iter,
+                                    stream);
             if (e != hipSuccess) return e;
         }
-        if (kw > 0) e = launch_refine_wave(v, n_block, n_small, kw, info, tol, max_iter, stream);
+        if (split.kmin > 1) e = launch_refine_wave(v, n_block, n_small, split, info, tol, max_iter, stream);
     }
     return e;
 }

@@ -56,3 +56,31 @@ def test_factorisation_of_spread_systems(precision, lo, hi, per_cu, tiling):
     which = "a64" if precision == 0 else "a32"
     for q in (0, len(sizes) // 3, len(sizes) - 1):
         assert np.array_equal(a.system(q, which)[0], b.system(q, which)[0]), q
+
+
+# K angles; `wave`: refined by a wavefront each, so the solutions are those of
+# the tiling that pins it.  The others differ from it in the last bits only.
+@pytest.mark.parametrize("n,per_cu,K,wave", [
+    (32, 2.0, 1, True), (64, 2.0, 1, False), (128, 2.5, 1, True), (24, 4.0, 2, False), (64, 8.0, 2, True),
+    (86, 6.0, 2, True), (96, 8.0, 2, False), (24, 5.0, 3, True), (48, 5.0, 3, False), (24, 5.0, 4, False)])
+def test_refinement(n, per_cu, K, wave):
+    B = int(per_cu * _cus())
+    # the same factors on both sides: the LU by wavefronts, which the second
+    # tiling pins, or by workgroups for small batches
+    a, b = (_solved([n] * B, [K] * B, 1, t) for t in (None, WAVE))
+    assert a.refine_iterations().max() <= 4
+    if np.array_equal(a.system(0, "a32")[0], b.system(0, "a32")[0]):
+        assert bool((a.gamma == b.gamma).all()) == wave
+    else:
+        assert n + 1 > 64 and per_cu <= 2.5   # (the order is n + 1)
+    assert float((a.gamma - b.gamma).abs().max()) < 1e-9 * float(b.gamma.abs().max())
+
+
+def test_refinement_of_mixed_angles():
+    # one to four angles each: both kernels take a share, every airfoil is
+    # refined once
+    sizes = [24, 32, 48, 64, 86, 88, 96, 128] * (5 * _cus() // 8)
+    ks = [1 + q // 8 % 4 for q in range(len(sizes))]
+    a, b = (_solved(sizes, ks, 1, t) for t in (None, WAVE))
+    assert a.refine_iterations().min() >= 1 and a.refine_iterations().max() <= 4
+    assert float((a.gamma - b.gamma).abs().max()) < 1e-9 * float(b.gamma.abs().max())
