@@ -226,10 +226,19 @@ __global__ __launch_bounds__(256) void assemble_kernel(WsView v, const double *_
 hipError_t launch_assemble(const WsView &v, int32_t B, int32_t max_cols, int32_t mixed,
                            const double *xy, const double *alpha, const double *chord, double vinf,
                            hipStream_t stream) {
-    // four chunks per workgroup share its set-up and leave no short wavefronts;
-    // one each while the batch is too small to give every CU a few workgroups
+    // Four chunks per workgroup share its set-up and leave no short wavefronts;
+    // with few sections, or chunks enough per section, the finer grid of one
+    // chunk each balances better.  One / four chunks per workgroup, us, FP64:
+    // N = 96, 128, 200: 4096, 2048, 1280 sections 246/183, 187/164, 266/227; N =
+    // 256: 256, 768, 1024, 2048 sections 68/69, 205/212, 311/302, 576/562; N = 319:
+    // 384, 512, 768 sections 158/172, 225/223, 364/351; N = 400: 1024 694/641.  So
+    // from 16384 chunks on (964 sections of N = 256, 781 of N = 319).  (Below that
+    // four win too for short sections: 256 of N = 200 55/48.)  Equal sections of
+    // more than 32 chunks hardly care (N = 512: 2048 1841/1846; N = 1024: 256
+    // 987/1008, 1024 3491/3583), large uneven batches up to such sections do:
+    // those from twice as many on.
     const int chunks = (max_cols + COLS - 1) / COLS;
-    if ((int64_t)B * chunks >= 16 * 2048) {
+    if ((int64_t)B * chunks >= (chunks <= 32 ? 16384 : 32768)) {
         dim3 grid(B, (chunks + 3) / 4);
         if (mixed)
             assemble_kernel<true, 4><<<grid, 256, 0, stream>>>(v, xy, alpha, chord, vinf);
