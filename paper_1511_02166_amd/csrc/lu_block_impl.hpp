@@ -631,6 +631,17 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
             }
     }
     auto ccol = [&](int t, int e) { return cs + 16 * t + LC * k4 + UC * e; };
+    // element (r, c) for a load of a round that runs past c1: in FP32 with
+    // rank-64 updates by a 32-bit offset from the system's base (a system is less
+    // than 2^23 bytes), whose registers the C tile of the next step leaves free
+    // (uneven batch of 4096, FP32 step: 7.78 -> 7.57 ms with the stores addressed
+    // by pointers all the same)
+    auto cedge = [&](int c, int r) {
+        if constexpr (NBLK == NBK)
+            return reinterpret_cast<T *>(reinterpret_cast<char *>(A) + (unsigned)(c * ld + r) * (unsigned)sizeof(T));
+        else
+            return A + ((size_t)c * ld + r);
+    };
     // staging: thread tid brings elements tid + TB e of a 16 RG x 16 NBLK tile
     // (rows fastest) into fragment order
     const int nit = (n - kend + 16 * RG - 1) / (16 * RG);
@@ -661,14 +672,15 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
                 for (int e = 0; e < 4; ++e) cb[t][e] = *cptr(t, e, r);
         } else {
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if constexpr (SB)
-                        cb[t][e] = A[(size_t)min(ccol(t, e), c1 - 1) * ld + r];
+                        cb[t][e] = *cedge(min(ccol(t, e), c1 - 1), r);
                     else
                         cb[t][e] = A[coff[t][e] + r];
                 }
+            }
         }
     };
     load_l(0);
@@ -681,11 +693,19 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
         if (it + 1 < nit) store_l((it + 1) & 1);
         load_l(it + 2);
         if (act) {
+            // C starts the sums: the first products take it down to the size of
+            // the Schur complement, which is far smaller for these smooth
+            // kernels, and the rounding of the others follows it down.  (Sums
+            // from zero with C added after them round at C's size throughout: the
+            // solutions of order 1025 were off by 2.5e-11 instead of 7e-13, of
+            // order 401 by 2.1e-12 instead of 1.6e-13, FP32 before refinement
+            // 6.3e-3 and 1.2e-3 instead of 8.6e-4 and 1.6e-4.)
             acc_t acc[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[t][e] = T(0);
+                for (int e = 0; e < 4; ++e) acc[t][e] = cb[t][e];
+            load_c(it + 1);   // (ahead of the products: 256 x 1025, FP64: 7.52 -> 7.07 ms)
             const vec_t *lt = reinterpret_cast<const vec_t *>(&S.u.tile[it & 1][rg][0]) + lane;
 #pragma unroll
             for (int sv = 0; sv < S4 / VW; ++sv) {
@@ -701,20 +721,19 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) *cptr(t, e, r) = cb[t][e] + acc[t][e];
+                        for (int e = 0; e < 4; ++e) *cptr(t, e, r) = acc[t][e];
                 } else {
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             if constexpr (SB) {
-                                if (ccol(t, e) < c1) A[(size_t)ccol(t, e) * ld + r] = cb[t][e] + acc[t][e];
+                                if (ccol(t, e) < c1) A[(size_t)ccol(t, e) * ld + r] = acc[t][e];
                             } else {
-                                if (cok[t][e]) A[coff[t][e] + r] = cb[t][e] + acc[t][e];
+                                if (cok[t][e]) A[coff[t][e] + r] = acc[t][e];
                             }
                 }
             }
-            load_c(it + 1);
         }
     }
     lds_barrier();   // the tiles are free again
