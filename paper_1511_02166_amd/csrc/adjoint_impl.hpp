@@ -2,8 +2,6 @@
 // workgroup per airfoil, any order up to NM (device functions only).
 #pragma once
 
-#include <climits>
-
 #include "fastmath.hpp"
 #include "panel_internal.hpp"
 #include "wave.hpp"
@@ -21,31 +19,6 @@ template <> __device__ inline const double *factors<double>(const WsView &v, con
 }
 template <> __device__ inline const float *factors<float>(const WsView &v, const AirfoilMeta &mt) {
     return v.a32 + mt.a_off;
-}
-
-// perm[i] = row of the system at position i of its factored form; all threads
-// call it.  Only the exchanges that move something are walked.
-__device__ __forceinline__ void perm_of_pivots(const int32_t *piv, int n, int tb, unsigned short *perm) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int i = tid; i < n; i += tb) perm[i] = (unsigned short)i;
-    __syncthreads();
-    if (tid < 64) {
-        for (int i0 = 0; i0 < n; i0 += 64) {
-            const int p = i0 + lane < n ? piv[i0 + lane] : i0 + lane;
-            unsigned long long m = __ballot(p != i0 + lane);
-            while (m) {
-                const int l = __ffsll((long long)m) - 1;
-                m &= m - 1;
-                const int q = __builtin_amdgcn_readlane(p, l);
-                if (lane == 0) {
-                    const unsigned short t = perm[i0 + l];
-                    perm[i0 + l] = perm[q];
-                    perm[q] = t;
-                }
-            }
-        }
-    }
-    __syncthreads();
 }
 
 // sum over 64 lanes, in T

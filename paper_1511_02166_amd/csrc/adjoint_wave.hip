@@ -23,8 +23,6 @@
 // |m_j - P_{i+1}|^2 is shared with the next panel, as in the assembly, and
 // each pair yields both the control-point term (accumulated per lane) and
 // the panel-end terms (summed over the wavefront once per panel).
-#include <climits>
-
 #include "fastmath.hpp"
 #include "panel_internal.hpp"
 #include "wave.hpp"

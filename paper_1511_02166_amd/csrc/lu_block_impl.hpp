@@ -62,10 +62,6 @@ constexpr int BSP = 64;         // super-panel width
 constexpr int NBK = BSP / NB;   // 16-row blocks of its band
 constexpr int RGM = 2;          // most row tiles in flight per LDS buffer
 
-// Barrier for exchanges through LDS: waits for this wavefront's LDS accesses
-// only, so global loads and stores stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // 32-bit order-preserving prefix of a = |value|: 1 for zero, larger for
 // larger values (0: no candidate).  Exact for FP32; for FP64 values that
 // share a high word (or lie below its range) share the prefix.

@@ -32,41 +32,12 @@ using wv::opaque_s;
 
 constexpr int SB = 64;     // rows per diagonal block in the triangular solves
 
-// Barrier for exchanges through LDS: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // Maximum over each row of 16 lanes, in all its lanes.
 __device__ __forceinline__ double row16_max(double v) {
     v = fmax(v, dpp_d<0xB1>(v));    // quad_perm [1,0,3,2]
     v = fmax(v, dpp_d<0x4E>(v));    // quad_perm [2,3,0,1]
     v = fmax(v, dpp_d<0x141>(v));   // row_half_mirror
     return fmax(v, dpp_d<0x140>(v));   // row_mirror
-}
-
-// perm[i] = row of the system at position i of its factored form, from the
-// sequence of exchanges; all threads call it.  Most pivots stay where they
-// are, so only the exchanges that move something are walked.
-__device__ __forceinline__ void perm_of_pivots(const int32_t *piv, int n, int tb, unsigned short *perm) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int i = tid; i < n; i += tb) perm[i] = (unsigned short)i;
-    __syncthreads();
-    if (tid < 64) {
-        for (int i0 = 0; i0 < n; i0 += 64) {
-            const int p = i0 + lane < n ? piv[i0 + lane] : i0 + lane;
-            unsigned long long m = __ballot(p != i0 + lane);
-            while (m) {
-                const int l = __ffsll((long long)m) - 1;
-                m &= m - 1;
-                const int q = __builtin_amdgcn_readlane(p, l);
-                if (lane == 0) {
-                    const unsigned short t = perm[i0 + l];
-                    perm[i0 + l] = perm[q];
-                    perm[q] = t;
-                }
-            }
-        }
-    }
-    __syncthreads();
 }
 
 // KG: right-hand sides per pass (4 or 8); NM: largest order.

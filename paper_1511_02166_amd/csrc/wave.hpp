@@ -1,5 +1,6 @@
 // wave.hpp -- wavefront-level primitives for gfx950 (64 lanes): DPP
-// exchanges inside 16-lane rows and scalar-register broadcasts.
+// exchanges inside 16-lane rows and scalar-register broadcasts; the workgroup
+// kernels' LDS barrier and pivot permutation.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,6 +48,36 @@ __device__ inline double wave_sum(double v) {
     v += dpp_d<0x141>(v);
     v += dpp_d<0x140>(v);
     return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
+}
+
+// Barrier for exchanges through LDS: waits for this wavefront's LDS accesses
+// only, so global loads and stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// perm[i] = row of the system at position i of its factored form, from the
+// sequence of exchanges; all threads call it.  Most pivots stay where they
+// are, so only the exchanges that move something are walked.
+__device__ __forceinline__ void perm_of_pivots(const int32_t *piv, int n, int tb, unsigned short *perm) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < n; i += tb) perm[i] = (unsigned short)i;
+    __syncthreads();
+    if (tid < 64) {
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int p = i0 + lane < n ? piv[i0 + lane] : i0 + lane;
+            unsigned long long m = __ballot(p != i0 + lane);
+            while (m) {
+                const int l = __ffsll((long long)m) - 1;
+                m &= m - 1;
+                const int q = __builtin_amdgcn_readlane(p, l);
+                if (lane == 0) {
+                    const unsigned short t = perm[i0 + l];
+                    perm[i0 + l] = perm[q];
+                    perm[q] = t;
+                }
+            }
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace panel
