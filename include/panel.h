@@ -40,9 +40,9 @@
  *      -1   non-finite node coordinate or zero-length panel; outputs NaN
  *      -2   mixed precision: refinement did not reach the tolerance within
  *           max_iter sweeps (the last iterate is returned)
- *      -3   the workspace's airfoil order sends a system to a kernel that
- *           cannot hold it (the plan changed after panel_workspace_init);
- *           outputs NaN
+ *      -3   the workspace's airfoil order does not match the plan (it changed
+ *           after panel_workspace_init) and gives a system a place among
+ *           smaller ones, whose kernels cannot hold it; outputs NaN
  */
 #ifndef PANEL_H
 #define PANEL_H
@@ -106,8 +106,11 @@ panel_status panel_plan_create(int32_t B, const int32_t *h_node_offsets,
 void panel_plan_destroy(panel_plan *plan);
 
 /* Choose the LU kernel by system order (Sec. 3: many independent dense
- * factorisations).  Systems with n1 = N_b + 1 <= max_n1 are factored by one
- * wavefront each; larger ones by a workgroup of four wavefronts each.
+ * factorisations).  Systems with n1 = N_b + 1 > max_n1 are factored by a
+ * workgroup of four or eight wavefronts each.  Those within the limit are
+ * factored by one wavefront each where there are enough of them to fill the
+ * GPU; in small batches the library gives them a workgroup each too, unless the
+ * tiling (below) sets wg_waves or persistent.
  *   max_n1   0 .. 320; 0 sends every system to the workgroup kernel.
  *            Default 320.
  * Both kernels produce LAPACK getrf factors and pivots (largest |a|, lowest
@@ -132,8 +135,9 @@ panel_status panel_plan_set_formulation(panel_plan *plan, int32_t formulation);
  * dense systems; Sec. 4 splits the population into slices, here the batch
  * is one queue).  This is the entry of the tile table that the Python
  * autotuner (PanelSolver.autotune) fills by timing candidates per batch.
- *   wave_max_n1  systems with n1 <= wave_max_n1 (0..320) are factored by one
- *                wavefront each, larger ones by a workgroup each
+ *   wave_max_n1  systems with n1 > wave_max_n1 (0..320) are factored by a
+ *                workgroup each; those within it by one wavefront each, but
+ *                for what wg_waves = 0 allows
  *   persistent   1: one launch of persistent workgroups pops the airfoils in
  *                LPT order, whole workgroups taking the large systems and
  *                single wavefronts the rest, and (PANEL_FP32_REFINE) refines
@@ -142,12 +146,18 @@ panel_status panel_plan_set_formulation(panel_plan *plan, int32_t formulation);
  *                wg_waves = 8, always take separate launches.
  *   wg_waves     wavefronts per workgroup-factored system: 4, 8, or 0 (eight
  *                when the batch has at most one airfoil per CU; systems above
- *                768 rows always take eight).  With 0, and persistent = 0,
- *                small batches also factor the systems within wave_max_n1 by
- *                a workgroup each, and refine them so where they have several
- *                angles
- * Default {320, 0, 0} (the faster choice on the batches measured; the
- * persistent kernel holds both paths and spills more registers).  Changing
+ *                768 rows always take eight).  With 0, in separate launches, the
+ *                library also chooses for the systems within wave_max_n1: a
+ *                workgroup each for the LU of small batches (up to about two
+ *                systems per CU, more where the orders differ widely); with
+ *                PANEL_FP32_REFINE a workgroup each for the refinement of
+ *                airfoils with several angles (in large batches of short
+ *                sections from three or four angles on) and of every airfoil
+ *                in small batches.  4 or 8 keeps them on the one-wavefront
+ *                kernels.
+ * Default {320, 0, 0}: within a few per cent of the fastest tiling on the
+ * batches measured (the autotuner finds what is left); the persistent kernel
+ * holds both paths and spills more registers.  Changing
  * wave_max_n1 takes effect at the next panel_workspace_init, as for
  * panel_plan_set_wave_limit.                                               */
 typedef struct {

@@ -195,7 +195,7 @@ def panel_plan_destroy(plan: Plan):
 
 
 def panel_plan_set_wave_limit(plan: Plan, max_n1: int):
-    """Largest system order factored by one wavefront (0..320; 0 = none)."""
+    """Largest system order that one wavefront may factor (0..320; 0 = none)."""
     _check(load_library().panel_plan_set_wave_limit(plan.handle, int(max_n1)))
 
 

@@ -33,8 +33,8 @@
 // What bounds it: FP64 vector arithmetic in the pairs, the serial chain of the
 // diagonal blocks in the transposed solve.  Measured against one evaluation
 // per control point and another per panel, with a lane per (strided) column
-// in the solve: 5.45 -> 1.97 ms for 256 sections of order 1025, 0.81 -> 0.61
-// ms for 1024 of order 257 (against one wavefront per section).
+// in the solve (HIP events): 5.48 -> 1.90 ms for 256 sections of order 1025,
+// 0.78 -> 0.54 ms for 1024 of order 257 (against one wavefront per section).
 #include "adjoint_impl.hpp"
 
 namespace panel {

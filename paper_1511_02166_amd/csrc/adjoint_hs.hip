@@ -33,8 +33,9 @@
 // the end.
 //
 // What bounds it: FP64 vector arithmetic.  Measured against an evaluation per
-// angle and a thread per row or node: 96 sections of order 181, two angles,
-// FP32 factors 1.05 -> 0.385 ms; 1024 of order 257, one angle 4.35 -> 2.27 ms.
+// angle and a thread per row or node (HIP events): 96 sections of order 181, two
+// angles with Cp cotangents, FP32 factors 0.99 -> 0.36 ms; 1024 of order 257, one
+// angle 4.31 -> 2.02 ms (FP32 factors), 2.75 -> 1.52 ms (FP64).
 #include "adjoint_impl.hpp"
 
 namespace panel {

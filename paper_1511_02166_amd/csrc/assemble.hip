@@ -27,8 +27,9 @@
 // past a multiple of 64.
 //
 // What bounds it: FP64 vector arithmetic (86 vector instructions per interior
-// entry).  4000 systems of order 201: 0.80 -> 0.66 ms, 2048 of order 257: 0.60 ->
-// 0.54 ms against a shorter table of arctangent centres and a block per chunk.
+// entry).  Within a step (HIP events), 4000 systems of order 201: 0.79 -> 0.58 ms,
+// 2048 of order 257: 0.55 -> 0.47 ms against a shorter table of arctangent centres
+// and a block per chunk.
 #include "fastmath.hpp"
 #include "panel_internal.hpp"
 

@@ -24,11 +24,11 @@ void launch(const WsView &v, int32_t count, int32_t n_block, int32_t waves, int3
             hipStream_t s) {
     constexpr int NTM = sizeof(T) == 8 ? 3 : 4;
     // Above 768 rows the trailing blocks' traffic counts: a rank-128 update
-    // halves it (256 systems of order 1025, eight angles: 8.0 -> 7.5 ms in
-    // FP64, 4.8 -> 4.6 ms in FP32); below, its longer band solves cost more
-    // (256 of order 513: 1.50 -> 1.64 ms).  Up to 512 rows an instance of two
-    // row slots spills less than one of three (1024 of order 401 in FP64:
-    // 2.85 -> 2.70 ms).
+    // halves it (256 systems of order 1025, eight angles: 7.98 -> 7.03 ms in
+    // FP64, 4.73 -> 4.57 ms in FP32); below, its longer band solves cost more
+    // (256 of order 513 in FP64: 1.49 -> 1.65 ms, in FP32 1.00 -> 1.06).  Up to
+    // 512 rows an instance of two row slots spills less than one of three (1024
+    // of order 401 in FP64: 2.97 -> 2.85 ms).
     if (waves == 8 && max_n1 > 768)
         lu_kernel<T, 3, 512, sizeof(T) == 8 ? 2 : 4, 2><<<count, 512, 0, s>>>(v, n_block, info);   // n1 <= 1536
     else if (waves == 8)

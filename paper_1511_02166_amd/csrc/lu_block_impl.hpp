@@ -35,12 +35,16 @@
 // them in one pass over U.
 //
 // What bounds it: 256 systems of order 1025 (one per CU) spend two thirds of
-// their time in the trailing update, at about half the FP64 matrix rate;
-// smaller systems wait in the pivot chain (about 1600 cycles per column).
-// Measured against a version with a thread per column for the triangular
-// solves, U staged in LDS and one right-hand side per back substitution: 14.9
-// -> 7.5 ms (256 x 1025, FP64, eight right-hand sides), 8.6 -> 4.6 ms in FP32,
-// 7.6 -> 4.35 ms (1980 systems of 321 to 513, FP32).
+// their time in the trailing update, at about half the FP64 matrix rate.  A
+// small system waits: one of order 161 (FP64, nine right-hand sides) takes 3140
+// cycles per column, 1410 of them in the pivot chain (search, exchange of the
+// candidates, rank-1 update), 440 loading panels with their left-looking update,
+// 430 storing them, moving rows and gathering the band, 440 in the trailing
+// update, 420 in the back substitution.
+// Measured (HIP events) against a version with a thread per column for the
+// triangular solves, U staged in LDS and one right-hand side per back
+// substitution: 14.7 -> 7.03 ms (256 x 1025, FP64, eight right-hand sides), 8.45
+// -> 4.57 ms in FP32, 7.60 -> 3.97 ms (1980 systems of 321 to 513, FP32).
 #pragma once
 
 #include <climits>
@@ -601,10 +605,9 @@ __device__ __forceinline__ void blk_round(T *A, int ld, int n, int kb, int kend,
     // C columns of this lane, col(lane, e) = lane part + uniform part.  In FP32
     // and in the rank-128 rounds, a round of whole columns reads each (t, e) at
     // a scalar base plus one per-lane offset, which saves two or three vector
-    // instructions per access (whole FP32 step of 256 sections of order 1025:
-    // 7.08 -> 6.94 ms, of the uneven batch of 4096 9.50 -> 9.42 ms);
-    // the other FP64 rounds, and those that run past c1, keep an element
-    // offset per column (one system of order 161: 227 us against 231).
+    // instructions per access (256 x 1025 in FP64: 7.50 -> 7.03 ms; 1980 systems
+    // of 321 to 513 in FP32: 4.10 -> 3.97); the other FP64 rounds keep an element
+    // offset per column (256 x 513: 1.49 ms against 1.57 at scalar bases).
     constexpr bool SB = sizeof(T) == 4 || NBLK > NBK;
     constexpr int LC = ColMap<T>::lane, UC = ColMap<T>::step;
     const bool whole = SB && cs + 16 * NT <= c1;   // wave-uniform

@@ -86,7 +86,8 @@ class PanelSolver:
         return self.plan.B
 
     def set_wave_limit(self, max_n1: int):
-        """Systems of order <= max_n1 go to the one-wavefront kernels (0..320)."""
+        """Systems of order > max_n1 (0..320) go to the workgroup kernels; the others to the
+        one-wavefront kernels where there are enough of them (panel_plan_set_wave_limit)."""
         B.panel_plan_set_wave_limit(self.plan, max_n1)
         B.panel_workspace_init(self.plan, self.ws)
         self.wave_limit = int(max_n1)
