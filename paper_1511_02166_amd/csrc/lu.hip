@@ -78,25 +78,30 @@ bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, in
     return n <= 224 ? spread >= 1.4 && per_cu <= 2.0 : spread >= 1.2 && per_cu <= 2.65;
 }
 
-// Refinement of the systems within the wave limit: a workgroup each where it
-// reads the matrix once for several right-hand sides, or where the batch leaves
-// most SIMDs idle.  Wavefronts / workgroups, us (with the same LU before them),
-// systems of one order:
-//   one angle, order 33, 129, 257: 1/CU 60/60, 261/237, 706/647;  2/CU 63/66,
-//   276/270, 861/802;  2.5/CU 69/90, 308/354, 921/964
-//   two angles, order 33, 65, 89, 97: 4/CU 101/104, 205/203, 262/239, 297/273;
-//   6/CU 116/134, 233/259, 299/304, 342/342;  16/CU 229/314, 512/628, 740/751,
-//   898/839
+// Fewest right-hand sides for which a workgroup refines a system within the wave
+// limit, instead of a wavefront: it reads the matrix once for several of them,
+// and a small batch leaves most SIMDs idle.  Wavefronts / workgroups, us (with the
+// same LU before them), systems of one order or of a range:
+//   one angle, order 33, 129, 257: 1/CU 60/60, 262/238, 707/648;  2/CU 63/66,
+//   276/270, 862/802;  2.5/CU 70/91, 309/354, 921/965
+//   two angles, order 33, 65, 89, 97: 4/CU 101/104, 205/204, 262/239, 297/274;
+//   6/CU 117/134, 233/260, 299/304, 343/342;  16/CU 230/314, 513/629, 741/752,
+//   898/839;  16/CU of orders 25 to 97: 422/512, 25 to 129: 690/654, 66 to 129:
+//   908/842 (rms orders 65, 83, 100)
 //   three angles, order 25, 33, 49: 8/CU 133/130, 167/167, 225/209;  16/CU
-//   236/252, 297/318, 407/398;  four angles, order 25: 16/CU 291/256; order 201:
-//   8/CU 2330/1349
-// A wavefront each where the tiling fixes the workgroups.
-RefineSplit refine_split(int32_t n_small, int32_t max_n1_small, int32_t wg_waves) {
-    const int32_t cus = device_cus();
-    if (wg_waves != 0) return {PANEL_KMAX + 1, 0, 0};
-    if (n_small <= 2 * cus && max_n1_small > 64) return {1, 0, 0};
-    if (n_small <= 4 * cus) return {2, 0, 0};
-    return {2, 88, 40};
+//   236/252, 298/319, 407/399;  16/CU of orders 25 to 97: 548/524
+//   four angles, order 25: 16/CU 291/256
+// The batch decides as a whole (the two kernels run one after the other: with an
+// order above 88 for workgroups, 16/CU of orders 25 to 97 took 477).  Tilings that
+// fix the workgroups keep the wavefronts.
+int32_t refine_kmin(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t wg_waves) {
+    const int32_t n = max_n1_small, cus = device_cus();
+    if (wg_waves != 0) return PANEL_KMAX + 1;
+    if (n_small <= 2 * cus && n > 64) return 1;
+    if (n_small <= 4 * cus) return 2;
+    const double rms2 = double(n) * n * small_eff / n_small;   // mean square order
+    if (rms2 > 92.0 * 92.0 || (rms2 > 80.0 * 80.0 && n > 112)) return 2;
+    return n > 40 ? 3 : 4;
 }
 
 }  // namespace
@@ -121,17 +126,16 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
     }
     if (e != hipSuccess) return e;
     if (mixed) {
-        const RefineSplit all{1, 0, 0};
-        e = launch_refine_block(v, 0, n_block, all, max_n1_block, max_k, waves, info, tol, max_iter, stream);
+        e = launch_refine_block(v, 0, n_block, 1, max_n1_block, max_k, waves, info, tol, max_iter, stream);
         if (e != hipSuccess) return e;
         const int32_t n_small = B - n_block;
-        const RefineSplit split = refine_split(n_small, max_n1_small, wg_waves);
-        if (refine_in_block(split, max_k, max_n1_small)) {
-            e = launch_refine_block(v, n_block, n_small, split, PANEL_WAVE_MAX_N1, max_k, 4, info, tol, max_iter,
+        const int32_t kmin = refine_kmin(n_small, max_n1_small, small_eff, wg_waves);
+        if (max_k >= kmin) {
+            e = launch_refine_block(v, n_block, n_small, kmin, PANEL_WAVE_MAX_N1, max_k, 4, info, tol, max_iter,
                                     stream);
             if (e != hipSuccess) return e;
         }
-        if (split.kmin > 1) e = launch_refine_wave(v, n_block, n_small, split, info, tol, max_iter, stream);
+        if (kmin > 1) e = launch_refine_wave(v, n_block, n_small, kmin - 1, info, tol, max_iter, stream);
     }
     return e;
 }

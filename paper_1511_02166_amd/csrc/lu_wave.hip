@@ -14,12 +14,12 @@ __global__ __launch_bounds__(WL, 2) void lu_wave_kernel(WsView v, int32_t first,
     wave_lu<T>(v, v.order[first + blockIdx.x], info_out, W);
 }
 
-__global__ __launch_bounds__(WL, 2) void refine_wave_kernel(WsView v, int32_t first, RefineSplit split,
+__global__ __launch_bounds__(WL, 2) void refine_wave_kernel(WsView v, int32_t first, int32_t kmax,
                                                          int32_t *__restrict__ info, double tol, int max_iter) {
     __shared__ WaveRefLds W;
     const int b = v.order[first + blockIdx.x];
     const AirfoilMeta mt = v.meta[b];
-    if (refine_in_block(split, mt.K, mt.n1)) return;
+    if (mt.K > kmax) return;
     if (mt.n1 > WL * PANEL_WAVE_RMAX) {
         // too large for one wavefront: the workspace's airfoil order does not
         // match the plan.  The factorisation has refused such a system already;
@@ -50,10 +50,10 @@ hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, const RefineSplit &split, int32_t *info,
+hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t kmax, int32_t *info,
                               double tol, int32_t max_iter, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    refine_wave_kernel<<<count, WL, 0, stream>>>(v, first, split, info, tol, max_iter);
+    refine_wave_kernel<<<count, WL, 0, stream>>>(v, first, kmax, info, tol, max_iter);
     return hipGetLastError();
 }
 

@@ -114,27 +114,20 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
                                int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream);
 hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t mixed, int32_t *info,
                           hipStream_t stream);
-// Which airfoils of a range a workgroup each refines, and which a wavefront
-// each: by right-hand sides (at least kmin) and, with two and three, by order.
-struct RefineSplit {
-    int32_t kmin, above2, above3;
-};
-inline __host__ __device__ bool refine_in_block(const RefineSplit &r, int32_t K, int32_t n1) {
-    return K >= r.kmin && n1 > (K == 2 ? r.above2 : K == 3 ? r.above3 : 0);
-}
-hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, const RefineSplit &split, int32_t *info,
-                              double tol, int32_t max_iter, hipStream_t stream);
+// (airfoils with more than kmax right-hand sides are left to another kernel)
+hipError_t launch_refine_wave(const WsView &v, int32_t first, int32_t count, int32_t kmax, int32_t *info, double tol,
+                              int32_t max_iter, hipStream_t stream);
 // Systems at the front of the order (orders up to max_n1; with four wavefronts
 // at most 768; those from n_block on within the wave limit), a workgroup of
 // `waves` (4 or 8) wavefronts each (lu_block.hip).
 hipError_t launch_lu_block(const WsView &v, int32_t count, int32_t n_block, int32_t waves, int32_t max_n1,
                            int32_t mixed, int32_t *info, hipStream_t stream);
 // `count` airfoils of the order from `first` on (orders up to max_n1; with four
-// wavefronts at most 768), those that `split` gives to workgroups
+// wavefronts at most 768), those with at least kmin right-hand sides
 // (refine_block.hip).
-hipError_t launch_refine_block(const WsView &v, int32_t first, int32_t count, const RefineSplit &split,
-                               int32_t max_n1, int32_t max_k, int32_t waves, int32_t *info, double tol,
-                               int32_t max_iter, hipStream_t stream);
+hipError_t launch_refine_block(const WsView &v, int32_t first, int32_t count, int32_t kmin, int32_t max_n1,
+                               int32_t max_k, int32_t waves, int32_t *info, double tol, int32_t max_iter,
+                               hipStream_t stream);
 // A whole batch in one persistent launch (lu_batch.hip).
 hipError_t launch_lu_batch(const WsView &v, int32_t grid, int32_t B, int32_t n_block, int32_t mixed, double tol,
                            int32_t max_iter, int32_t *info, hipStream_t stream);

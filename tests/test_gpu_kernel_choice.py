@@ -84,3 +84,18 @@ def test_refinement_of_mixed_angles():
     a, b = (_solved(sizes, ks, 1, t) for t in (None, WAVE))
     assert a.refine_iterations().min() >= 1 and a.refine_iterations().max() <= 4
     assert float((a.gamma - b.gamma).abs().max()) < 1e-9 * float(b.gamma.abs().max())
+
+
+# orders of a range, two angles: one kernel refines the whole batch, so either
+# every solution or none is that of the tiling which pins the wavefronts
+@pytest.mark.parametrize("lo,hi,wave", [(24, 96, True), (24, 128, False)])
+def test_refinement_of_spread_systems(lo, hi, wave):
+    sizes = list(np.linspace(lo // 2, hi // 2, 8 * _cus()).astype(int) * 2)
+    a, b = (_solved(sizes, [2] * len(sizes), 1, t) for t in (None, WAVE))
+    for q in (0, len(sizes) // 2, len(sizes) - 1):
+        assert np.array_equal(a.system(q, "a32")[0], b.system(q, "a32")[0]), q
+    off = np.concatenate([[0], np.cumsum(2 * np.asarray(sizes))])
+    assert a.gamma.numel() == off[-1]
+    same = [bool((a.gamma[i:j] == b.gamma[i:j]).all()) for i, j in zip(off[:-1], off[1:])]
+    assert all(same) if wave else not all(same[:len(same) // 2])
+    assert float((a.gamma - b.gamma).abs().max()) < 1e-9 * float(b.gamma.abs().max())
