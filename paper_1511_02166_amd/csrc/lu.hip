@@ -91,9 +91,11 @@ bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, in
 //   three angles, order 25, 33, 49: 8/CU 133/130, 167/167, 225/209;  16/CU
 //   236/252, 298/319, 407/399;  16/CU of orders 25 to 97: 548/524
 //   four angles, order 25: 16/CU 291/256
-// The batch decides as a whole (the two kernels run one after the other: with an
-// order above 88 for workgroups, 16/CU of orders 25 to 97 took 477).  Tilings that
-// fix the workgroups keep the wavefronts.
+// The batch decides as a whole, as the two kernels run one after the other.  A
+// line through the batch (two angles above order 88, three above 40, for
+// workgroups) / the batch: two angles, orders 25 to 97, 8/CU 332/291, 16/CU
+// 489/429; 65 to 101, 6/CU 376/303; 65 to 128, 8/CU 529/454; three angles, orders
+// 25 to 112, 8/CU 404/339.  Tilings that fix the workgroups keep the wavefronts.
 int32_t refine_kmin(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t wg_waves) {
     const int32_t n = max_n1_small, cus = device_cus();
     if (wg_waves != 0) return PANEL_KMAX + 1;
