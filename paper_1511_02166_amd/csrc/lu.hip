@@ -82,8 +82,9 @@ bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, in
 // limit, instead of a wavefront: it reads the matrix once for several of them,
 // and a small batch leaves most SIMDs idle.  Wavefronts / workgroups, us (with the
 // same LU before them), systems of one order or of a range:
-//   one angle, order 33, 129, 257: 1/CU 60/60, 262/238, 707/648;  2/CU 63/66,
-//   276/270, 862/802;  2.5/CU 70/91, 309/354, 921/965
+//   one angle, order 25, 33, 49, 129, 257: 0.25/CU 47/45, 60/60, 80/78, 236/226,
+//   696/638;  1/CU 48/47, 60/60, 82/81, 262/238, 707/648;  2/CU 50/51, 63/66,
+//   87/88, 276/270, 862/802;  2.5/CU 52/68, 70/91, 98/120, 309/354, 921/965
 //   two angles, order 33, 65, 89, 97: 4/CU 101/104, 205/204, 262/239, 297/274;
 //   6/CU 117/134, 233/260, 299/304, 343/342;  16/CU 230/314, 513/629, 741/752,
 //   898/839;  16/CU of orders 25 to 97: 422/512, 25 to 129: 690/654, 66 to 129:
@@ -96,10 +97,12 @@ bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, in
 // workgroups) / the batch: two angles, orders 25 to 97, 8/CU 332/291, 16/CU
 // 489/429; 65 to 101, 6/CU 376/303; 65 to 128, 8/CU 529/454; three angles, orders
 // 25 to 112, 8/CU 404/339.  Tilings that fix the workgroups keep the wavefronts.
-int32_t refine_kmin(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t wg_waves) {
+// Beside airfoils with more angles, those with one go to workgroups as well up to
+// two per CU: a launch for them alone costs 2 us where the whole takes 50 to 100.
+int32_t refine_kmin(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t max_k, int32_t wg_waves) {
     const int32_t n = max_n1_small, cus = device_cus();
     if (wg_waves != 0) return PANEL_KMAX + 1;
-    if (n_small <= 2 * cus && n > 64) return 1;
+    if (n_small <= cus || (n_small <= 2 * cus && (n > 64 || max_k > 1))) return 1;
     if (n_small <= 4 * cus) return 2;
     const double rms2 = double(n) * n * small_eff / n_small;   // mean square order
     if (rms2 > 92.0 * 92.0 || (rms2 > 80.0 * 80.0 && n > 112)) return 2;
@@ -131,7 +134,7 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
         e = launch_refine_block(v, 0, n_block, 1, max_n1_block, max_k, waves, info, tol, max_iter, stream);
         if (e != hipSuccess) return e;
         const int32_t n_small = B - n_block;
-        const int32_t kmin = refine_kmin(n_small, max_n1_small, small_eff, wg_waves);
+        const int32_t kmin = refine_kmin(n_small, max_n1_small, small_eff, max_k, wg_waves);
         if (max_k >= kmin) {
             e = launch_refine_block(v, n_block, n_small, kmin, PANEL_WAVE_MAX_N1, max_k, 4, info, tol, max_iter,
                                     stream);

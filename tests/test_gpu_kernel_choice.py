@@ -61,7 +61,8 @@ def test_factorisation_of_spread_systems(precision, lo, hi, per_cu, tiling):
 # K angles; `wave`: refined by a wavefront each, so the solutions are those of
 # the tiling that pins it.  The others differ from it in the last bits only.
 @pytest.mark.parametrize("n,per_cu,K,wave", [
-    (32, 2.0, 1, True), (64, 2.0, 1, False), (128, 2.5, 1, True), (24, 4.0, 2, False), (64, 8.0, 2, True),
+    (24, 0.25, 1, False), (48, 1.0, 1, False), (32, 2.0, 1, True), (64, 2.0, 1, False),
+    (128, 2.5, 1, True), (24, 4.0, 2, False), (64, 8.0, 2, True),
     (86, 6.0, 2, True), (96, 8.0, 2, False), (24, 5.0, 3, True), (48, 5.0, 3, False), (24, 5.0, 4, False)])
 def test_refinement(n, per_cu, K, wave):
     B = int(per_cu * _cus())
