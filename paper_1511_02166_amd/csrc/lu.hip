@@ -68,14 +68,37 @@ bool eight_waves(int32_t n_block, int32_t max_n1, int32_t wg_waves) {
 //   FP32, 24-104: 1.70: 195/210;  24-128: 1.61: 273/263, 1.93: 279/310;  128-200:
 //   1.61: 489/467, 2.14: 554/565;  150-256: 2.52: 920/866;  200-256: 1.75:
 //   857/785, 2.49: 937/919;  200-319: 2.64: 1316/1230;  24-319: 2.16: 1243/1132, 2.92: 1401/1415
-bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, int32_t mixed) {
+// (All with one angle.)  Each further angle costs a wavefront more than a
+// workgroup, whose back substitution takes all of them in one pass: the limits
+// grow with the mean number of angles k (small_rhs), and in FP32 equal systems
+// pay too from some k on.  Wavefronts over workgroups, time:
+//   FP32, one order, 2.1 to 3/CU: order 97, k = 4, 8, 12: 0.91 1.02 1.09;  129,
+//   k = 2, 4, 8: 0.89 0.97 1.11;  193, k = 2, 4, 8: 0.97 1.05 1.11;  289, k = 1, 2,
+//   3, 4, 8: 0.96 0.99 1.03 1.06 1.16
+//   FP32, orders of a range: 24-104, 1.70: k = 1, 3, 4: 0.92 1.00 1.03;  65-104
+//   (spread 1.48), 1.85: k = 4, 8: 0.94 1.05;  65-128, 2.37: k = 2, 3, 4: 0.95 1.00
+//   1.04;  100-143, 2.00: k = 2, 4: 0.91 1.00;  24-200, 2.32: k = 1, 2, 3: 0.94 0.97
+//   1.01;  200-319, 2.70: k = 1: 1.08
+//   FP64: 24-104, 1.35: k = 1, 2, 3, 4: 0.88 0.94 1.00 1.06;  65-104, 1.40: k = 4,
+//   6: 0.93 1.02
+// (From three systems per CU on wavefronts, though twelve angles of order 257
+// would take 1.23 at 3.5; in FP64 the limits above 112 stay those of one angle.)
+bool small_in_blocks(int32_t n_small, int32_t max_n1_small, double small_eff, double small_rhs, int32_t mixed) {
     const int32_t n = max_n1_small, cus = device_cus();
     if (n <= (mixed ? 64 : 96)) return false;
     const double per_cu = small_eff / cus, spread = n_small / small_eff;
     if (n_small <= 2 * cus) return mixed || n > 112 || per_cu <= 1.6;
-    if (!mixed) return spread >= 1.4 && per_cu <= (n <= 112 ? 1.2 : n <= 224 ? 1.5 : 2.25);
-    if (n <= 144) return spread >= 1.5 && per_cu <= 1.65;
-    return n <= 224 ? spread >= 1.4 && per_cu <= 2.0 : spread >= 1.2 && per_cu <= 2.65;
+    const double k = small_rhs, more = k - 1.0;
+    if (!mixed) {
+        if (n > 112) return spread >= 1.4 && per_cu <= (n <= 224 ? 1.5 : 2.25);
+        return per_cu <= 1.5 && (spread >= 1.9 ? per_cu <= 1.2 + 0.08 * more : k >= 6.0);
+    }
+    if (per_cu > 3.0) return false;
+    if (k >= (n <= 126 ? 8.0 : n <= 152 ? 5.0 : n <= 272 ? 4.0 : 3.0)) return true;
+    if (n <= 112) return spread >= 1.9 && per_cu <= 1.4 + 0.1 * more;
+    if (n > 224) return spread >= 1.2 && per_cu <= 2.85 + 0.15 * more;
+    if (spread < (k < 3.0 ? 1.4 : 1.2)) return false;
+    return per_cu <= (n <= 144 ? 1.6 + 0.15 * more : 2.0 + 0.2 * more);
 }
 
 // Fewest right-hand sides for which a workgroup refines a system within the wave
@@ -112,8 +135,9 @@ int32_t refine_kmin(int32_t n_small, int32_t max_n1_small, double small_eff, int
 }  // namespace
 
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
-                               int32_t max_n1_small, double small_eff, int32_t max_k, int32_t mixed, double tol,
-                               int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream) {
+                               int32_t max_n1_small, double small_eff, double small_rhs, int32_t max_k,
+                               int32_t mixed, double tol, int32_t max_iter, int32_t *info, int32_t persistent,
+                               int32_t wg_waves, hipStream_t stream) {
     hipError_t e = hipSuccess;
     if (persistent && (n_block == 0 || !eight_waves(n_block, max_n1_block, wg_waves == 0 ? 4 : wg_waves))) {
         const int n_small = B - n_block;
@@ -121,7 +145,7 @@ hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int3
         return launch_lu_batch(v, grid, B, n_block, mixed, tol, max_iter, info, stream);
     }
     const int32_t waves = eight_waves(n_block, max_n1_block, wg_waves) ? 8 : 4;
-    if (wg_waves == 0 && small_in_blocks(B - n_block, max_n1_small, small_eff, mixed)) {
+    if (wg_waves == 0 && small_in_blocks(B - n_block, max_n1_small, small_eff, small_rhs, mixed)) {
         // every system by a workgroup, in one launch
         e = launch_lu_block(v, B, n_block, n_block > 0 && eight_waves(B, max_n1_block, 0) ? 8 : 4,
                             n_block > 0 ? max_n1_block : max_n1_small, mixed, info, stream);

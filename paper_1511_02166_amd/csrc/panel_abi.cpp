@@ -31,6 +31,7 @@ struct panel_plan {
     int32_t max_n1_block = 0;  // their largest order
     int32_t max_n1_small = 0;  // the largest order of the others
     double small_eff = 0.0;    // their number, each weighted by (order / largest order)^2
+    double small_rhs = 0.0;    // their mean number of right-hand sides, with the same weights
     // set when the wave limit changed after the last panel_workspace_init:
     // the airfoil order in the workspace no longer matches n_block
     mutable bool order_stale = false;
@@ -116,6 +117,7 @@ void build_order(panel_plan *p) {
     p->max_n1_block = 0;
     p->max_n1_small = 0;
     p->small_eff = 0.0;
+    p->small_rhs = 0.0;
     for (int32_t b = 0; b < B; ++b) {
         order[b] = b;
         const int32_t n1 = p->node_off[b + 1] - p->node_off[b];
@@ -126,9 +128,13 @@ void build_order(panel_plan *p) {
         } else {
             p->max_n1_small = std::max(p->max_n1_small, n1);
             p->small_eff += double(n1) * n1;
+            p->small_rhs += double(n1) * n1 * (p->alpha_off[b + 1] - p->alpha_off[b]);
         }
     }
-    if (p->max_n1_small > 0) p->small_eff /= double(p->max_n1_small) * p->max_n1_small;
+    if (p->max_n1_small > 0) {
+        p->small_rhs /= p->small_eff;
+        p->small_eff /= double(p->max_n1_small) * p->max_n1_small;
+    }
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t c) {
         if (big[a] != big[c]) return big[a] > big[c];
         return p->cost[a] > p->cost[c];
@@ -380,7 +386,7 @@ panel_status panel_factor_solve(const panel_plan *plan, void *ws, double refine_
         return fail(PANEL_EINVAL, "wave limit changed: call panel_workspace_init before factoring");
     WsView v = ws_view(ws, plan->layout);
     hipError_t e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, plan->max_n1_small,
-                                       plan->small_eff, plan->max_k, mixed, refine_tol,
+                                       plan->small_eff, plan->small_rhs, plan->max_k, mixed, refine_tol,
                                        max_iter, info, plan->tiling.persistent, plan->tiling.wg_waves,
                                        static_cast<hipStream_t>(stream));
     return check_hip(e, "factor/solve launch");
@@ -465,7 +471,7 @@ panel_status panel_solve_noalloc(const panel_plan *plan, const double *xy, const
             : launch_assemble(v, plan->B, plan->max_cols, mixed, xy, alpha, chord, vinf, s);
     if (e != hipSuccess) return check_hip(e, "assembly launch");
     e = launch_factor_solve(v, plan->B, plan->n_block, plan->max_n1_block, plan->max_n1_small,
-                                       plan->small_eff, plan->max_k, mixed, refine_tol, max_iter, info,
+                            plan->small_eff, plan->small_rhs, plan->max_k, mixed, refine_tol, max_iter, info,
                             plan->tiling.persistent, plan->tiling.wg_waves, s);
     if (e != hipSuccess) return check_hip(e, "factor/solve launch");
     e = plan->formulation == PANEL_HESS_SMITH ? launch_forces_hs(v, plan->B, plan->max_k, gamma, cp, cl, cl_p, s)

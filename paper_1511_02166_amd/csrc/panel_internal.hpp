@@ -108,10 +108,12 @@ constexpr int PANEL_WAVE_MAX_N1 = 64 * PANEL_WAVE_RMAX;
 // wg_waves != 8.  wg_waves: 4 or 8 wavefronts per workgroup-kernel system,
 // 0 = eight when the batch has at most one airfoil per CU.  max_n1_small: the
 // largest order among the others; small_eff: their number, each weighted by
-// (order / max_n1_small)^2; max_k: the most right-hand sides of an airfoil.
+// (order / max_n1_small)^2; small_rhs: their mean number of right-hand sides,
+// weighted alike; max_k: the most right-hand sides of an airfoil.
 hipError_t launch_factor_solve(const WsView &v, int32_t B, int32_t n_block, int32_t max_n1_block,
-                               int32_t max_n1_small, double small_eff, int32_t max_k, int32_t mixed, double tol,
-                               int32_t max_iter, int32_t *info, int32_t persistent, int32_t wg_waves, hipStream_t stream);
+                               int32_t max_n1_small, double small_eff, double small_rhs, int32_t max_k,
+                               int32_t mixed, double tol, int32_t max_iter, int32_t *info, int32_t persistent,
+                               int32_t wg_waves, hipStream_t stream);
 hipError_t launch_lu_wave(const WsView &v, int32_t first, int32_t count, int32_t mixed, int32_t *info,
                           hipStream_t stream);
 // (airfoils with more than kmax right-hand sides are left to another kernel)

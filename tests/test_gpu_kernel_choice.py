@@ -58,6 +58,20 @@ def test_factorisation_of_spread_systems(precision, lo, hi, per_cu, tiling):
         assert np.array_equal(a.system(q, which)[0], b.system(q, which)[0]), q
 
 
+
+# K angles: the line moves with them (orders of one size, or from lo to hi)
+@pytest.mark.parametrize("precision,lo,hi,per_cu,K,tiling", [
+    (1, 318, 318, 2.5, 4, BLOCK), (1, 318, 318, 2.5, 2, WAVE), (1, 318, 318, 3.1, 4, WAVE), (1, 192, 192, 2.1, 4, BLOCK),
+    (1, 128, 128, 2.5, 8, BLOCK), (1, 128, 128, 2.5, 4, WAVE), (1, 64, 64, 2.1, 8, BLOCK), (1, 64, 64, 2.1, 4, WAVE),
+    (1, 24, 104, 4.0, 5, BLOCK), (1, 24, 104, 4.0, 1, WAVE), (0, 24, 104, 3.2, 4, BLOCK), (0, 24, 104, 3.2, 1, WAVE)])
+def test_factorisation_with_several_angles(precision, lo, hi, per_cu, K, tiling):
+    sizes = np.linspace(lo // 2, hi // 2, int(per_cu * _cus())).astype(int) * 2
+    a, b = (_solved(list(sizes), [K] * len(sizes), precision, t) for t in (None, tiling))
+    which = "a64" if precision == 0 else "a32"
+    for q in (0, len(sizes) // 3, len(sizes) - 1):
+        assert np.array_equal(a.system(q, which)[0], b.system(q, which)[0]), q
+
+
 # K angles; `wave`: refined by a wavefront each, so the solutions are those of
 # the tiling that pins it.  The others differ from it in the last bits only.
 @pytest.mark.parametrize("n,per_cu,K,wave", [
