@@ -149,7 +149,8 @@ panel_status panel_plan_set_formulation(panel_plan *plan, int32_t formulation);
  *                768 rows always take eight).  With 0, in separate launches, the
  *                library also chooses for the systems within wave_max_n1: a
  *                workgroup each for the LU of small batches (up to about two
- *                systems per CU, more where the orders differ widely); with
+ *                systems per CU, more where the orders differ widely and, with
+ *                PANEL_FP32_REFINE, with several angles); with
  *                PANEL_FP32_REFINE a workgroup each for the refinement of
  *                airfoils with several angles (in large batches of short
  *                sections from three or four angles on) and of every airfoil
